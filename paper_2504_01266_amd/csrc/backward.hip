@@ -5,6 +5,7 @@
 
 #include <cstring>
 
+#include "bank_f32.hpp"
 #include "f2d_host.hpp"
 #include "f2d_internal.hpp"
 #include "grad_internal.hpp"
@@ -64,12 +65,36 @@ size_t frame_bytes(const Problem& pr) {
                   frame_plane_size(pr.image.h, pr.image.w, r) * sizeof(float));
 }
 
+namespace {
+
+size_t partial_bytes(int64_t sets, int k) {
+  const size_t bytes = static_cast<size_t>(sets) * k * k * sizeof(float);
+  return round_up(bytes > 0 ? bytes : 1);
+}
+
+// Units of the matrix-core grad_filter.  The workspace stays within the
+// static scratch of filter2d_backward_noalloc wherever the one-pair plan's
+// does, and is no larger than that plan's elsewhere.
+BankF32WgradPlan bank_plan(const Problem& pr) {
+  const f2d_tensor& im = pr.image;
+  const FilterPlan fp = filter_plan(pr);
+  const size_t set = static_cast<size_t>(fp.nf > 0 ? fp.nf : 1) * pr.k * pr.k * sizeof(float);
+  const size_t frame = frame_bytes(pr), scratch = F2D_NOALLOC_SCRATCH_BYTES - 256;
+  const int64_t room = frame < scratch ? static_cast<int64_t>((scratch - frame) / set) : 0;
+  const int64_t base = fp.nrep * fp.chunks;
+  BankF32WgradPlan plan;
+  bank_f32_wgrad_plan(im.n, im.h, im.w, pr.c_out, im.c, room > base ? room : base, &plan);
+  return plan;
+}
+
+}  // namespace
+
 size_t backward_workspace(const Problem& pr) {
   if (pr.image.dtype == F2D_BF16) return bank_backward_bf16_workspace(pr);
   if (pr.image.dtype != F2D_F32) return 0;
   const FilterPlan fp = filter_plan(pr);
-  const size_t bytes = static_cast<size_t>(fp.n_units) * pr.k * pr.k * sizeof(float);
-  return frame_bytes(pr) + round_up(bytes > 0 ? bytes : 1);
+  const bool mfma = bank_f32_wgrad_mfma(pr.mode, pr.k, pr.c_out, pr.image.c, pr.image.w);
+  return frame_bytes(pr) + partial_bytes(mfma ? bank_plan(pr).sets * fp.nf : fp.n_units, pr.k);
 }
 
 f2d_status check_backward(const Problem& pr, const f2d_tensor* grad_outs, int32_t n_grad_outs,
@@ -118,7 +143,52 @@ f2d_status run_backward(const Problem& pr, const f2d_tensor* grad_outs, int32_t 
   const bool empty = im.n == 0 || im.c == 0 || im.h == 0 || im.w == 0 || co == 0;
 
   // ---------------------------------------------------------- grad_input --
-  if (grad_input && !empty) {
+  if (grad_input && !empty && bank_f32_conv_mfma(pr.mode, K, pr.c_out, im.c, im.w)) {
+    const f2d_tensor& g = grad_outs[0];
+    const int64_t r = (K - 1) / 2;
+    BankF32Params p;
+    std::memset(&p, 0, sizeof(p));
+    p.src = static_cast<const float*>(g.data);
+    p.s_sn = g.stride_n;
+    p.s_sc = g.stride_c;
+    p.s_sh = g.stride_h;
+    p.dst = static_cast<float*>(grad_input->data);
+    p.d_sn = grad_input->stride_n;
+    p.d_sc = grad_input->stride_c;
+    p.d_sh = grad_input->stride_h;
+    p.w = static_cast<const float*>(pr.filter.data);
+    p.w_so = K * K;
+    p.w_sc = im.c * K * K;
+    p.H = im.h;
+    p.W = im.w;
+    p.row0 = -r;  // the image and its r-wide frame, from a 4-aligned column
+    p.rows = im.h + 2 * r;
+    p.col0 = r > 0 ? -4 : 0;
+    p.xend = im.w + r;
+    p.n_img = im.n;
+    p.CI = static_cast<int32_t>(pr.c_out);
+    p.CO = static_cast<int32_t>(im.c);
+    p.zero = 1;
+    p.fr = static_cast<int32_t>(r);
+    p.frame = static_cast<float*>(ws);
+    p.frame_plane = frame_plane_size(im.h, im.w, r);
+    hipError_t err = launch_bank_f32_conv(p, K, true, s);
+    if (err != hipSuccess) return hip_status(err, "grad_input launch");
+    FoldParams fo;
+    fo.frame = p.frame;
+    fo.frame_plane = p.frame_plane;
+    fo.out = p.dst;
+    fo.out_sn = p.d_sn;
+    fo.out_sc = p.d_sc;
+    fo.out_sh = p.d_sh;
+    fo.H = im.h;
+    fo.W = im.w;
+    fo.r = r;
+    fo.planes = im.n * im.c;
+    fo.groups = im.c;
+    err = launch_fold_frame(fo, s);
+    if (err != hipSuccess) return hip_status(err, "grad_input edge launch");
+  } else if (grad_input && !empty) {
     StencilParams p;
     std::memset(&p, 0, sizeof(p));
     EdgeParams e;
@@ -224,7 +294,34 @@ f2d_status run_backward(const Problem& pr, const f2d_tensor* grad_outs, int32_t 
   if (grad_filter) {
     const FilterPlan fp = filter_plan(pr);
     float* partial = reinterpret_cast<float*>(static_cast<char*>(ws) + frame_bytes(pr));
-    if (!empty) {
+    if (!empty && bank_f32_wgrad_mfma(pr.mode, K, pr.c_out, im.c, im.w)) {
+      const f2d_tensor& g = grad_outs[0];
+      BankF32WgradParams q;
+      std::memset(&q, 0, sizeof(q));
+      q.x = static_cast<const float*>(im.data);
+      q.x_sn = im.stride_n;
+      q.x_sc = im.stride_c;
+      q.x_sh = im.stride_h;
+      q.g = static_cast<const float*>(g.data);
+      q.g_sn = g.stride_n;
+      q.g_sc = g.stride_c;
+      q.g_sh = g.stride_h;
+      q.partial = partial;
+      q.H = im.h;
+      q.W = im.w;
+      q.n_img = im.n;
+      q.CI = static_cast<int32_t>(im.c);
+      q.CO = static_cast<int32_t>(pr.c_out);
+      const BankF32WgradPlan plan = bank_plan(pr);
+      q.runs = plan.runs;
+      q.run_rows = plan.run_rows;
+      q.strip_runs = plan.strip_runs;
+      q.run_strips = plan.run_strips;
+      hipError_t err = launch_bank_f32_wgrad(q, K, s);
+      if (err == hipSuccess)
+        err = launch_reduce_partials(partial, grad_filter, fp.nf, K * K, plan.sets, 1, s);
+      return hip_status(err, "grad_filter launch");
+    } else if (!empty) {
       GradFilterParams q;
       std::memset(&q, 0, sizeof(q));
       q.x = im.data;

@@ -4,6 +4,7 @@
 
 #include <cstring>
 
+#include "bank_f32.hpp"
 #include "f2d_host.hpp"
 #include "f2d_internal.hpp"
 
@@ -104,7 +105,36 @@ f2d_status forward_f32_zero(const Problem& pr, const f2d_tensor* outs, hipStream
   return go(p);
 }
 
+// FP32 bank on the matrix cores (either border).
+f2d_status forward_bank_f32(const Problem& pr, const f2d_tensor& out, hipStream_t s) {
+  const f2d_tensor& im = pr.image;
+  BankF32Params p;
+  std::memset(&p, 0, sizeof(p));
+  p.src = static_cast<const float*>(im.data);
+  p.s_sn = im.stride_n;
+  p.s_sc = im.stride_c;
+  p.s_sh = im.stride_h;
+  p.dst = static_cast<float*>(out.data);
+  p.d_sn = out.stride_n;
+  p.d_sc = out.stride_c;
+  p.d_sh = out.stride_h;
+  p.w = static_cast<const float*>(pr.filter.data);
+  p.w_so = im.c * pr.k * pr.k;
+  p.w_sc = pr.k * pr.k;
+  p.H = im.h;
+  p.W = im.w;
+  p.row0 = pr.row_begin;
+  p.rows = pr.rows;
+  p.xend = im.w;
+  p.n_img = im.n;
+  p.CI = static_cast<int32_t>(im.c);
+  p.CO = static_cast<int32_t>(pr.c_out);
+  p.zero = pr.opts.border == F2D_BORDER_ZERO ? 1 : 0;
+  return hip_status(launch_bank_f32_conv(p, pr.k, false, s), "forward f32 bank launch");
+}
+
 f2d_status forward_f32(const Problem& pr, const f2d_tensor* outs, int32_t n_outs, hipStream_t s) {
+  if (bank_f32_conv_mfma(pr.mode, pr.k, pr.image.c, pr.c_out, pr.image.w)) return forward_bank_f32(pr, outs[0], s);
   if (pr.opts.border == F2D_BORDER_ZERO) return forward_f32_zero(pr, outs, s);
   const int K = pr.k;
   const bool templ = K <= kMaxTemplK;
