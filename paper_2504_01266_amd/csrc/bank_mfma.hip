@@ -55,6 +55,10 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// the same at any element-aligned address (odd widths, odd strides)
+typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kThreads = 256;      // wgrad work-group
 constexpr int kTH = 4;             // conv tile rows
@@ -89,8 +93,7 @@ struct BankParams {
   float* frame;
   int64_t frame_plane;
   int32_t fr;
-  int32_t d_vec;  // output rows and planes 16-byte (f32) / 8-byte (bf16) aligned
-  int32_t s_vec;  // source rows and planes 16-byte aligned and W % 8 == 0 (vector staging)
+  int32_t s_vec;  // W >= 8: staging by 8-column chunks, else by elements (VEC = false kernels)
   int32_t s_plan32;  // s_vec, and one image of the source spans < 2^31 elements with H, s_sh < 2^24
 };
 
@@ -222,11 +225,15 @@ struct Raw<float, NT> {
   }
 };
 
-// 8 consecutive elements from a 16-byte aligned address
-__device__ __forceinline__ void load_vec(const uint16_t* a, u32x4& out) { out = *reinterpret_cast<const u32x4*>(a); }
+// 8 consecutive elements from any element-aligned address.  Rows need not be
+// 16-byte aligned: element loads for odd widths or strides held the 3x3
+// forward of 8 x 16 x 509 x 763 -> 64 (BF16 out) at 0.37 ms.
+__device__ __forceinline__ void load_vec(const uint16_t* a, u32x4& out) {
+  out = *reinterpret_cast<const u32x4_a2*>(a);
+}
 __device__ __forceinline__ void load_vec(const float* a, float (&out)[8]) {
-  const float4 x = reinterpret_cast<const float4*>(a)[0];
-  const float4 y = reinterpret_cast<const float4*>(a)[1];
+  const f32x4_a4 x = reinterpret_cast<const f32x4_a4*>(a)[0];
+  const f32x4_a4 y = reinterpret_cast<const f32x4_a4*>(a)[1];
   out[0] = x.x;
   out[1] = x.y;
   out[2] = x.z;
@@ -237,9 +244,42 @@ __device__ __forceinline__ void load_vec(const float* a, float (&out)[8]) {
   out[7] = y.w;
 }
 
+// A chunk that crosses or lies outside an end of the row is staged from the
+// nearest chunk inside it.  chunk_shift: how many columns right of that chunk
+// it starts (1..8, 8 and more alike), 0 for a chunk inside the row, -1 for one
+// left of it (chunks start at multiples of 8, so it lies outside whole).
+__device__ __forceinline__ int chunk_shift(int64_t gx0, int64_t W) {
+  if (gx0 < 0) return -1;
+  const int64_t s = gx0 - (W - 8);
+  return s <= 0 ? 0 : (s < 8 ? static_cast<int>(s) : 8);
+}
+// Element e of the result is element e + s of d, or the 16-bit value twice in
+// `fill` past the last one (0 <= s <= 8).
+__device__ __forceinline__ u32x4 shift_chunk(u32x4 d, int s, uint32_t fill) {
+  if (s & 8) d = u32x4{fill, fill, fill, fill};
+  if (s & 4) d = u32x4{d[2], d[3], fill, fill};
+  if (s & 2) d = u32x4{d[1], d[2], d[3], fill};
+  if (s & 1)
+    d = u32x4{__builtin_amdgcn_alignbit(d[1], d[0], 16), __builtin_amdgcn_alignbit(d[2], d[1], 16),
+              __builtin_amdgcn_alignbit(d[3], d[2], 16), __builtin_amdgcn_alignbit(fill, d[3], 16)};
+  return d;
+}
+// The chunk at shift s from the loaded one: clamped columns, or zeros outside
+// the row.  BRANCH: test for the shifts 1..7 (widths that are not a multiple
+// of 8) before computing them; measured faster in the ring kernels only.
+template <bool ZERO, bool BRANCH = false>
+__device__ __forceinline__ u32x4 edge_chunk(u32x4 d, int s) {
+  // (opaque, or the compiler keeps the tests of every chunk of a loop in
+  // scalar registers across the loop and spills)
+  asm volatile("" : "+v"(s));
+  const uint32_t fill = ZERO ? 0u : (s < 0 ? d[0] & 0xffffu : d[3] >> 16) * 0x10001u;
+  if (BRANCH && !(s > 0 && s < 8)) return u32x4{fill, fill, fill, fill};
+  return shift_chunk(d, s < 0 ? 8 : s, fill);
+}
+
 // 8 consecutive elements of a row starting at column gx0 from element loads
-// at clamped columns (zero outside the row for the adjoint): unaligned rows
-// or widths that are not a multiple of 8.
+// at clamped columns (zero outside the row for the adjoint): rows of fewer
+// than 8 columns.
 template <bool ADJ>
 __device__ __forceinline__ void load_chunk(const uint16_t* row, int64_t gx0, int64_t W, u32x4& out) {
   {
@@ -269,12 +309,14 @@ __device__ __forceinline__ void load_chunk(const float* row, int64_t gx0, int64_
 
 // Loads for tile rows ly0 .. ly0+NR-1 (of the LH staged rows) of the tile at
 // (oy0, ox0).
-template <typename G, int K, int CG, bool ADJ, typename TS, int SW = G::THREADS / 64, int NR = G::LH>
+// VEC = false (rows of fewer than 8 columns): element loads, in a kernel of
+// their own (a second producer of the staged registers beside the vector
+// loads made those wait for each other).
+template <typename G, int K, int CG, bool ADJ, typename TS, int SW = G::THREADS / 64, int NR = G::LH, bool VEC = true>
 __device__ __forceinline__ void stage_load(const BankParams& p, int64_t n, int64_t oy0, int64_t ox0,
                                            int wave, int lane, Raw<TS, staging_nt<G, SW, NR>()>& st, int ly0 = 0) {
   const TS* sp = static_cast<const TS*>(p.src) + n * p.s_sn;
   const int j = lane >> 3;
-  const bool vec = p.s_vec != 0;
 #pragma unroll
   for (int it = 0; it < staging_nt<G, SW, NR>(); ++it) {
     int ly, cg, chunk;
@@ -286,12 +328,15 @@ __device__ __forceinline__ void stage_load(const BankParams& p, int64_t n, int64
     const int c = cg * 8 + j;
     const TS* row = sp + static_cast<int64_t>(c < p.CI ? c : p.CI - 1) * p.s_sc + gy * p.s_sh;
     const int64_t gx0 = ox0 - 8 + 8 * chunk;
-    if (vec) {
-      // aligned rows, W a multiple of 8: every chunk lies left of, inside or
-      // right of the row, so one 16-byte load of the nearest chunk inside it
-      // always serves; stage_store fixes up the outside chunks
+    if constexpr (VEC) {
+      // one 16-byte load of the nearest chunk inside the row always serves;
+      // stage_store fixes up the chunks at its ends
       const int64_t gxl = gx0 < 0 ? 0 : (gx0 > p.W - 8 ? p.W - 8 : gx0);
       load_vec(row + gxl, st.v[it]);
+      // one unit's addresses and load at a time (interleaved by the compiler:
+      // BF16-out 3x3 forward 0.73 -> 0.76 ms, 5x5 dgrad from FP32 1.84 -> 2.05 ms
+      // at 16 x 16 x 1024^2 -> 64)
+      __builtin_amdgcn_sched_barrier(0);
     } else {
       load_chunk<ADJ>(row, gx0, p.W, st.v[it]);
     }
@@ -343,7 +388,7 @@ __device__ __forceinline__ u32x4 transpose8(u32x4 d, int j) {
 // LDS holds the rows as a ring of NSLOT rows: tile row ly sits in LDS row
 // (slot0 + ly) mod NSLOT.
 template <typename G, int K, int CG, bool ADJ, typename TS, int SW = G::THREADS / 64, int NR = G::LH,
-          bool RING = false>
+          bool RING = false, bool VEC = true, bool FIX = false>
 __device__ __forceinline__ void stage_store_unit(const BankParams& p, int64_t oy0, int64_t ox0, int wave, int lane,
                                                  const Raw<TS, staging_nt<G, SW, NR>()>& st, uint16_t* __restrict__ sl,
                                                  int it, int ly0 = 0, int slot0 = 0) {
@@ -364,13 +409,16 @@ __device__ __forceinline__ void stage_store_unit(const BankParams& p, int64_t oy
       keep = keep && gy >= 0 && gy < p.H;
     }
     u32x4 d = st.pairs(it);
-    if (p.s_vec) {  // chunks outside the row: edge value (clamp) or zero (adjoint)
+    if constexpr (VEC) {  // chunks outside the row: edge value (clamp) or zero (adjoint)
       const int64_t gx0 = ox0 - 8 + 8 * chunk;
-      if (gx0 < 0 || gx0 >= p.W) {
+      if constexpr (FIX) {
+        d = shift_chunk(d, chunk_shift(gx0, p.W), ADJ ? 0u : (d[3] >> 16) * 0x10001u);
+      } else if (gx0 < 0 || gx0 >= p.W) {
         const uint32_t e = gx0 < 0 ? (d[0] & 0xffffu) : (d[3] >> 16);
         const uint32_t b = ADJ ? 0u : (e | (e << 16));
         d = u32x4{b, b, b, b};
       }
+      if constexpr (FIX) act = act && gx0 < p.W && gx0 + 8 > p.W;
     }
     if (!keep) d = u32x4{0u, 0u, 0u, 0u};
     d = transpose8(d, j);  // channels cg*8 .. cg*8+7 of pixel chunk*8 + j
@@ -378,14 +426,31 @@ __device__ __forceinline__ void stage_store_unit(const BankParams& p, int64_t oy
   }
 }
 
+// The chunk that crosses the row's right end (W not a multiple of 8), written
+// again with its columns in place: stage_store_unit leaves it as loaded, so
+// that the common case has no branch between the MFMAs it runs among.  Once
+// per tile, after the tile's units and before its registers are reloaded.
 template <typename G, int K, int CG, bool ADJ, typename TS, int SW = G::THREADS / 64, int NR = G::LH,
-          bool RING = false>
+          bool RING = false, bool VEC = true>
+__device__ __forceinline__ void stage_fix(const BankParams& p, int64_t oy0, int64_t ox0, int wave, int lane,
+                                          const Raw<TS, staging_nt<G, SW, NR>()>& st, uint16_t* __restrict__ sl,
+                                          int ly0 = 0, int slot0 = 0) {
+  if (!VEC || p.W % 8 == 0 || ox0 + G::TW + 8 <= p.W) return;  // uniform
+  asm volatile("" : "+v"(lane));  // (recomputed here, not kept from the units)
+#pragma unroll
+  for (int it = 0; it < staging_nt<G, SW, NR>(); ++it)
+    stage_store_unit<G, K, CG, ADJ, TS, SW, NR, RING, VEC, true>(p, oy0, ox0, wave, lane, st, sl, it, ly0, slot0);
+}
+
+template <typename G, int K, int CG, bool ADJ, typename TS, int SW = G::THREADS / 64, int NR = G::LH,
+          bool RING = false, bool VEC = true, bool WHOLE = false>
 __device__ __forceinline__ void stage_store(const BankParams& p, int64_t oy0, int64_t ox0, int wave, int lane,
                                             const Raw<TS, staging_nt<G, SW, NR>()>& st, uint16_t* __restrict__ sl,
                                             int ly0 = 0, int slot0 = 0) {
 #pragma unroll
   for (int it = 0; it < staging_nt<G, SW, NR>(); ++it)
-    stage_store_unit<G, K, CG, ADJ, TS, SW, NR, RING>(p, oy0, ox0, wave, lane, st, sl, it, ly0, slot0);
+    stage_store_unit<G, K, CG, ADJ, TS, SW, NR, RING, VEC>(p, oy0, ox0, wave, lane, st, sl, it, ly0, slot0);
+  if constexpr (!WHOLE) stage_fix<G, K, CG, ADJ, TS, SW, NR, RING, VEC>(p, oy0, ox0, wave, lane, st, sl, ly0, slot0);
 }
 
 // LDS offset (elements) of tap t in the channels-last tile, relative to the
@@ -443,9 +508,9 @@ __device__ __forceinline__ void store4(void* dst, int64_t o, const f32x4& v) {
   if constexpr (OUT_BF16) {
     const uint32_t lo = pack_bf16x2(v[0], v[1]);
     const uint32_t hi = pack_bf16x2(v[2], v[3]);
-    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(dst) + o) = make_uint2(lo, hi);
+    *reinterpret_cast<u32x2_a2*>(static_cast<uint16_t*>(dst) + o) = u32x2{lo, hi};
   } else {
-    *reinterpret_cast<float4*>(static_cast<float*>(dst) + o) = make_float4(v[0], v[1], v[2], v[3]);
+    *reinterpret_cast<f32x4_a4*>(static_cast<float*>(dst) + o) = v;
   }
 }
 template <bool OUT_BF16>
@@ -465,7 +530,7 @@ __device__ __forceinline__ void store_px4(const BankParams& p, int64_t n, int co
                                           const f32x4& v) {
   if (oy >= p.rows || co >= p.CO) return;
   const int64_t iy = ADJ ? p.row0 + oy : oy;  // adjoint: image row
-  const bool inside = p.d_vec && (!ADJ || (iy >= 0 && iy < p.H && ox_l >= 0)) && ox_l + 4 <= p.W;
+  const bool inside = (!ADJ || (iy >= 0 && iy < p.H && ox_l >= 0)) && ox_l + 4 <= p.W;
   if (inside) {
     store4<OUT_BF16>(p.dst, n * p.d_sn + static_cast<int64_t>(co) * p.d_sc + iy * p.d_sh + ox_l, v);
     return;
@@ -497,7 +562,7 @@ template <bool ADJ, bool OUT_BF16, int OTP, int HP>
 __device__ __forceinline__ void store_acc(const BankParams& p, int64_t n, int co0, int64_t oy, int64_t oxw, int q,
                                           const f32x4 (&acc)[OTP][HP]) {
   const int64_t iy = ADJ ? p.row0 + oy : oy;
-  const bool fast = p.d_vec && oy < p.rows && (!ADJ || (iy >= 0 && iy < p.H && oxw >= 0)) && oxw + 16 * HP <= p.W;
+  const bool fast = oy < p.rows && (!ADJ || (iy >= 0 && iy < p.H && oxw >= 0)) && oxw + 16 * HP <= p.W;
   if (fast) {  // uniform
     const int64_t base = n * p.d_sn + iy * p.d_sh + oxw + 4 * q;
 #pragma unroll
@@ -673,6 +738,7 @@ __global__ __launch_bounds__(64 * NW) void k_bank_conv(BankParams p) {
       // is done reading (uniform branch)
       if (og2 != og || G::NBUF == 1) __syncthreads();
       if (og2 != og) load_weights<G, K, OT, CG, ADJ>(p, og2, tid, wl);
+      if constexpr (G::NBUF == 2) stage_fix<G, K, CG, ADJ, TS>(p, oy2, ox2, wave, lane, st, sl_next);
       if constexpr (G::NBUF == 1) stage_store<G, K, CG, ADJ, TS>(p, oy2, ox2, wave, lane, st, sl0);
     }
     __syncthreads();  // tile t+1 staged; everyone done with buffer cur
@@ -711,12 +777,14 @@ template <int NTN>
 struct RingPlan {
   uint32_t soff[NTN];  // element offset of the unit's chunk in image n, row 0
   uint32_t loff[NTN];  // LDS element offset within a ring row
-  uint32_t info[NTN];  // row (bits 0-7) | active << 8 | channel kept << 9 | outside (1 left, 2 right) << 10
+  bool edge;           // the tile column touches an end of the rows (uniform)
+  uint32_t info[NTN];  // row (bits 0-7) | active << 8 | channel kept << 9 | (1 + chunk_shift) << 10
 };
 
 template <typename G, int CG, int NR, int NTN>
 __device__ __forceinline__ void ring_plan(const BankParams& p, int64_t ox0, int wave, int lane, RingPlan<NTN>& pl) {
   const int j = lane >> 3;
+  pl.edge = ox0 < 8 || ox0 + G::TW + 8 > p.W;
 #pragma unroll
   for (int it = 0; it < NTN; ++it) {
     int ly, cg, chunk;
@@ -727,10 +795,10 @@ __device__ __forceinline__ void ring_plan(const BankParams& p, int64_t ox0, int 
     const int64_t cc = keep ? c : p.CI - 1;
     const int64_t gx0 = ox0 - 8 + 8 * chunk;
     const int64_t gxl = gx0 < 0 ? 0 : (gx0 > p.W - 8 ? p.W - 8 : gx0);
-    const uint32_t outside = gx0 < 0 ? 1u : (gx0 >= p.W ? 2u : 0u);
+    const uint32_t shift = static_cast<uint32_t>(1 + chunk_shift(gx0, p.W));
     pl.soff[it] = static_cast<uint32_t>(cc * p.s_sc + gxl);
     pl.loff[it] = static_cast<uint32_t>((chunk * 8 + j) * G::PS + cg * 8);
-    pl.info[it] = static_cast<uint32_t>(ly) | (act ? 1u << 8 : 0u) | (keep ? 1u << 9 : 0u) | (outside << 10);
+    pl.info[it] = static_cast<uint32_t>(ly) | (act ? 1u << 8 : 0u) | (keep ? 1u << 9 : 0u) | (shift << 10);
   }
 }
 
@@ -766,11 +834,9 @@ __device__ __forceinline__ void ring_store_unit(const BankParams& p, int64_t gy_
     keep = keep && gy >= 0 && gy < p.H;
   }
   u32x4 d = st.pairs(it);
-  const uint32_t outside = (info >> 10) & 3u;
-  if (outside) {  // chunks outside the row: edge value (clamp) or zero (adjoint)
-    const uint32_t e = outside == 1u ? (d[0] & 0xffffu) : (d[3] >> 16);
-    const uint32_t b = ADJ ? 0u : (e | (e << 16));
-    d = u32x4{b, b, b, b};
+  if (pl.edge) {  // uniform: edge value (clamp) or zero (adjoint)
+    const int shift = static_cast<int>((info >> 10) & 15u) - 1;
+    if (shift) d = edge_chunk<ADJ, true>(d, shift);
   }
   if (!keep) d = u32x4{0u, 0u, 0u, 0u};
   d = transpose8(d, j);
@@ -779,7 +845,7 @@ __device__ __forceinline__ void ring_store_unit(const BankParams& p, int64_t gy_
   if ((info >> 8) & 1u) *reinterpret_cast<u32x4*>(ring + lrow * (G::LW * G::PS) + pl.loff[it]) = d;
 }
 
-template <int K, int OT, int PT, int CG, bool ADJ, typename TS, bool OUT_BF16>
+template <int K, int OT, int PT, int CG, bool ADJ, typename TS, bool OUT_BF16, bool VEC>
 __global__ __launch_bounds__(512) void k_bank_conv_ring(BankParams p) {
   using G = ConvGeom<K, OT, PT, CG, 8>;
   static_assert(G::RINGED && G::NBUF == 1, "64-channel sources with one LDS tile");
@@ -835,14 +901,14 @@ __global__ __launch_bounds__(512) void k_bank_conv_ring(BankParams p) {
     {
       Raw<TS, staging_nt<G, 8, G::LH>()> sa;
       const int64_t oy0 = static_cast<int64_t>(ty0) * kTH;
-      stage_load<G, K, CG, ADJ, TS, 8, G::LH>(p, n, oy0, ox0, swave, slane, sa, 0);
-      stage_store<G, K, CG, ADJ, TS, 8, G::LH, true>(p, oy0, ox0, swave, slane, sa, ring, 0, 0);
+      stage_load<G, K, CG, ADJ, TS, 8, G::LH, VEC>(p, n, oy0, ox0, swave, slane, sa, 0);
+      stage_store<G, K, CG, ADJ, TS, 8, G::LH, true, VEC>(p, oy0, ox0, swave, slane, sa, ring, 0, 0);
     }
     int slot = 0;
     __syncthreads();
     constexpr int NTN = staging_nt<G, 8, NEW>();
     Raw<TS, NTN> st;
-    const bool planned = p.s_plan32 != 0;  // uniform
+    const bool planned = VEC && p.s_plan32 != 0;  // uniform
     RingPlan<NTN> pl;
     if (planned) ring_plan<G, CG, NEW, NTN>(p, ox0, wave, lane, pl);
     const TS* sp_n = static_cast<const TS*>(p.src) + n * p.s_sn;
@@ -858,7 +924,7 @@ __global__ __launch_bounds__(512) void k_bank_conv_ring(BankParams p) {
         if (planned)
           ring_load<TS, NTN>(p, sp_n, gy_next, pl, st);
         else
-          stage_load<G, K, CG, ADJ, TS, 8, NEW>(p, n, oy0 + kTH, ox0, swave, slane, st, G::LH - NEW);
+          stage_load<G, K, CG, ADJ, TS, 8, NEW, VEC>(p, n, oy0 + kTH, ox0, swave, slane, st, G::LH - NEW);
       }
       __builtin_amdgcn_sched_barrier(0);
       // ring row of this wave's tap row u (uniform), then the lane's pixel
@@ -891,7 +957,7 @@ __global__ __launch_bounds__(512) void k_bank_conv_ring(BankParams p) {
                 if (planned)
                   ring_store_unit<G, ADJ, TS, NEW, NTN>(p, gy_next, lane, pl, st, ring, u, nslot);
                 else
-                  stage_store_unit<G, K, CG, ADJ, TS, 8, NEW, true>(p, oy0 + kTH, ox0, swave, slane, st, ring, u,
+                  stage_store_unit<G, K, CG, ADJ, TS, 8, NEW, true, VEC>(p, oy0 + kTH, ox0, swave, slane, st, ring, u,
                                                                    G::LH - NEW, nslot);
               }
             }
@@ -901,13 +967,18 @@ __global__ __launch_bounds__(512) void k_bank_conv_ring(BankParams p) {
         store_acc<ADJ, OUT_BF16, OTP, HP>(p, n, co0, oy0 + wrow, ox0 + wcol, q, acc);
       });
       if (more) {
+        if constexpr (OVL || LATE) {
+          if (!planned)
+            stage_fix<G, K, CG, ADJ, TS, 8, NEW, true, VEC>(p, oy0 + kTH, ox0, swave, slane, st, ring, G::LH - NEW,
+                                                            nslot);
+        }
         __syncthreads();  // (OVL, LATE: the new rows are packed; all reads of the oldest rows done)
         if constexpr (!OVL && !LATE) {  // the oldest kTH ring rows become the next tile's new rows
           if (planned) {
 #pragma unroll
             for (int u = 0; u < NTN; ++u) ring_store_unit<G, ADJ, TS, NEW, NTN>(p, gy_next, lane, pl, st, ring, u, nslot);
           } else {
-            stage_store<G, K, CG, ADJ, TS, 8, NEW, true>(p, oy0 + kTH, ox0, swave, slane, st, ring, G::LH - NEW,
+            stage_store<G, K, CG, ADJ, TS, 8, NEW, true, VEC>(p, oy0 + kTH, ox0, swave, slane, st, ring, G::LH - NEW,
                                                         nslot);
           }
           __syncthreads();
@@ -1083,7 +1154,7 @@ __global__ __launch_bounds__(512) void k_bank_conv_vr(BankParams p) {
         for (int y = 0; y < HR; ++y) v[y] = (half ? acc[HR + y] : acc[y]) + *reinterpret_cast<const f32x4*>(rb + (mine + y) * 256);
         const int64_t oxw = ox0 + 16 * cb, ya = oy0 + mine, yb = ya + HR - 1;
         const int64_t iya = ADJ ? p.row0 + ya : ya, iyb = ADJ ? p.row0 + yb : yb;
-        const bool all_fast = p.d_vec && yb < p.rows && (!ADJ || (iya >= 0 && iyb < p.H && oxw >= 0)) &&
+        const bool all_fast = yb < p.rows && (!ADJ || (iya >= 0 && iyb < p.H && oxw >= 0)) &&
                               oxw + 16 <= p.W;
         if (all_fast) {  // uniform
           if (l16 < p.CO) {
@@ -1149,7 +1220,9 @@ struct WsGeom {
   static __device__ __forceinline__ int swz(int c) { return (c >> 2) & 3; }
 };
 
-template <int K, int CG>
+// WHOLE: W is a multiple of 8 (no chunk crosses the row's end; the fix pass
+// alone cost the 3x3 forward 1%).
+template <int K, int CG, bool WHOLE>
 __global__ __launch_bounds__(64 * (kWsMfma + kWsMem)) void k_bank_conv_ws(BankParams p) {
   using WG = WsGeom<K, CG>;
   using G = typename WG::G;
@@ -1207,8 +1280,8 @@ __global__ __launch_bounds__(64 * (kWsMfma + kWsMem)) void k_bank_conv_ws(BankPa
       const int64_t ox = hox + 32 * h + m * WG::EPC;
       if (co >= p.CO) continue;
       char* dp = static_cast<char*>(p.dst) + (hn * p.d_sn + static_cast<int64_t>(co) * p.d_sc + oy * p.d_sh + ox) * 2;
-      if (ox + WG::EPC <= p.W && (reinterpret_cast<uintptr_t>(dp) & 15) == 0) {
-        *reinterpret_cast<u32x4*>(dp) = v;
+      if (ox + WG::EPC <= p.W) {
+        *reinterpret_cast<u32x4_a2*>(dp) = v;
       } else {
 #pragma unroll
         for (int e = 0; e < WG::EPC; ++e)
@@ -1274,7 +1347,7 @@ __global__ __launch_bounds__(64 * (kWsMfma + kWsMem)) void k_bank_conv_ws(BankPa
   // of tile t+2 are issued right after tile t+1 is packed, a tile ahead
   Raw<uint16_t, WG::NTM> st;
   stage_load<G, K, CG, false, uint16_t, kWsMem>(p, n, oy0, ox0, mw, lane, st);
-  stage_store<G, K, CG, false, uint16_t, kWsMem>(p, oy0, ox0, mw, lane, st, sl0);
+  stage_store<G, K, CG, false, uint16_t, kWsMem, G::LH, false, true, WHOLE>(p, oy0, ox0, mw, lane, st, sl0);
   {
     const int64_t t1 = t + gridDim.x < p.n_tiles ? t + gridDim.x : t;
     int64_t n1, oy1, ox1;
@@ -1297,7 +1370,7 @@ __global__ __launch_bounds__(64 * (kWsMfma + kWsMem)) void k_bank_conv_ws(BankPa
       if (have) store_results(ri ^ 1, hn, hco, hoy, hox);
       // pack tile t+1 (loaded a tile ago; tile t again at the end, harmless)
       // and start the loads of tile t+2
-      stage_store<G, K, CG, false, uint16_t, kWsMem>(p, oy2, ox2, mw, lane, st, sl0 + (cur ^ 1) * G::S_ELEMS);
+      stage_store<G, K, CG, false, uint16_t, kWsMem, G::LH, false, true, WHOLE>(p, oy2, ox2, mw, lane, st, sl0 + (cur ^ 1) * G::S_ELEMS);
       const int64_t t3 = t_next + gridDim.x < p.n_tiles ? t_next + gridDim.x : (more ? t_next : t);
       int64_t n3, oy3, ox3;
       int og3;
@@ -1341,7 +1414,6 @@ struct WgradParams {
   int64_t H, W;
   int32_t CI, CO;
   int32_t tiles_x, tiles_y;
-  int32_t x_vec, g_vec;  // rows 16-byte aligned (x) / 16-byte-per-8-elements (g)
   int64_t n_tiles;       // N * tiles_y * tiles_x
   int32_t units;         // grid size: unit u takes tiles u, u + units, ...
 };
@@ -1378,11 +1450,11 @@ __device__ __forceinline__ bf16x8 window8(const uint32_t (&w)[12]) {
 
 // eight upstream-gradient values of one row as a bf16 A fragment
 __device__ __forceinline__ bf16x8 g_fragment(const uint16_t* src) {
-  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(src));
+  return __builtin_bit_cast(bf16x8, u32x4(*reinterpret_cast<const u32x4_a2*>(src)));
 }
 __device__ __forceinline__ bf16x8 g_fragment(const float* src) {
-  const float4 a = reinterpret_cast<const float4*>(src)[0];
-  const float4 b = reinterpret_cast<const float4*>(src)[1];
+  const f32x4_a4 a = reinterpret_cast<const f32x4_a4*>(src)[0];
+  const f32x4_a4 b = reinterpret_cast<const f32x4_a4*>(src)[1];
   const float f[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
   u32x4 r;
 #pragma unroll
@@ -1392,30 +1464,19 @@ __device__ __forceinline__ bf16x8 g_fragment(const float* src) {
 }
 
 // A fragments of this lane for one 32-pixel step: G-bar[o][y0 + m][xb .. xb+7]
-// for the tile's rows m, zero outside the image or past C_out.
-template <typename TG>
+// for the tile's rows m, zero outside the image.  `inside`: the whole tile's
+// columns are inside it.  Padded channels (o >= C_out) repeat the last one;
+// their sums are not written.
+template <typename TG, bool VEC>
 __device__ __forceinline__ void load_g(const WgradParams& p, const TG* gp, int o, int64_t y0, int64_t xb,
-                                       bool fast, bf16x8 (&ga)[kWgTH]) {
-  if (fast && y0 + kWgTH <= p.H) {  // uniform
-    // every row inside the image: plain loads with nothing applied to the
-    // values (a select on each loaded row here made every load wait for the
-    // previous one: 2.84 -> 2.37 ms for the 5x5 bank once removed)
+                                       bool inside, bf16x8 (&ga)[kWgTH]) {
+  if constexpr (!VEC) {  // rows of fewer than 8 columns: by elements
+    const TG* src = gp + (o < p.CO ? o : p.CO - 1) * p.g_sc;
 #pragma unroll
-    for (int m = 0; m < kWgTH; ++m) ga[m] = g_fragment(gp + o * p.g_sc + (y0 + m) * p.g_sh + xb);
-    return;
-  }
-#pragma unroll
-  for (int m = 0; m < kWgTH; ++m) {
-    const int64_t y = y0 + m;
-    if (fast) {
-      // rows past H are zeroed
-      const int64_t yc = y < p.H ? y : p.H - 1;
-      const bf16x8 v = g_fragment(gp + o * p.g_sc + yc * p.g_sh + xb);
-      ga[m] = y < p.H ? v : bf16x8{};
-    } else {
+    for (int m = 0; m < kWgTH; ++m) {
       u32x4 r = u32x4{0u, 0u, 0u, 0u};
-      if (o < p.CO && y < p.H) {
-        const TG* row = gp + o * p.g_sc + y * p.g_sh;
+      if (y0 + m < p.H) {
+        const TG* row = src + (y0 + m) * p.g_sh;
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
           uint32_t lo = 0, hi = 0;
@@ -1425,6 +1486,21 @@ __device__ __forceinline__ void load_g(const WgradParams& p, const TG* gp, int o
         }
       }
       ga[m] = __builtin_bit_cast(bf16x8, r);
+    }
+    return;
+  }
+  // the nearest rows and chunk inside the image, every load issued before
+  // any value is touched (a select on each loaded row here made every load
+  // wait for the previous one: 2.84 -> 2.37 ms for the 5x5 bank once removed)
+  const TG* src = gp + (o < p.CO ? o : p.CO - 1) * p.g_sc + (xb <= p.W - 8 ? xb : p.W - 8);
+#pragma unroll
+  for (int m = 0; m < kWgTH; ++m) ga[m] = g_fragment(src + (y0 + m < p.H ? y0 + m : p.H - 1) * p.g_sh);
+  if (!inside || y0 + kWgTH > p.H) {  // uniform: zero what lies outside
+    const int shift = chunk_shift(xb, p.W);
+#pragma unroll
+    for (int m = 0; m < kWgTH; ++m) {
+      const u32x4 w = shift_chunk(__builtin_bit_cast(u32x4, ga[m]), shift, 0u);
+      ga[m] = y0 + m < p.H ? __builtin_bit_cast(bf16x8, w) : bf16x8{};
     }
   }
 }
@@ -1488,8 +1564,8 @@ __device__ __forceinline__ void wg_rows(f32x4 (&acc)[K * K], const bf16x8 (&ga)[
 // K*K taps (acc).  Per tile: stage the clamped X tile in LDS (channel planes,
 // 16-byte chunks), then for each 32-pixel step hold the 8 G-bar row
 // fragments in registers and sweep the LH source rows once.
-template <int K, typename TG>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_bank_wgrad(WgradParams p) {
+template <int K, typename TG, bool VEC>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(K <= 3 ? 3 : 2))) void k_bank_wgrad(WgradParams p) {
   using G = WgGeom<K>;
   static_assert(G::R <= 4, "K <= 9");
   __shared__ uint4 xs4[(G::ELEMS + 7) / 8];
@@ -1512,7 +1588,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     const uint16_t* xp = p.x + n * p.x_sn;
     const TG* gp = static_cast<const TG*>(p.g) + n * p.g_sn;
     // X tile [ci][row][col], clamped; LDS column c <-> source column x0 - 8 + c
-    const bool x_fast = p.x_vec && x0 - 8 >= 0 && x0 + kWgTW + 8 <= p.W;
+    const bool x_in = x0 - 8 >= 0 && x0 + kWgTW + 8 <= p.W;  // uniform: every chunk inside the row
     u32x4 sv[(G::STAGE + kThreads - 1) / kThreads];
 #pragma unroll
     for (int it = 0; it < (G::STAGE + kThreads - 1) / kThreads; ++it) {
@@ -1524,22 +1600,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
       const int ci = c < p.CI ? c : p.CI - 1;
       const uint16_t* row = xp + ci * p.x_sc + gy * p.x_sh;
       const int64_t gx = x0 - 8 + 8 * ch;
-      if (x_fast) {
-        sv[it] = *reinterpret_cast<const u32x4*>(row + gx);
-      } else {
-        uint32_t h[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          int64_t cx = gx + e;
-          cx = cx < 0 ? 0 : (cx >= p.W ? p.W - 1 : cx);
-          h[e] = row[cx];
-        }
-        sv[it] = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
-      }
+      if constexpr (VEC)
+        load_vec(row + (gx < 0 ? 0 : (gx > p.W - 8 ? p.W - 8 : gx)), sv[it]);
+      else
+        load_chunk<false>(row, gx, p.W, sv[it]);
     }
-    const bool g_fast = p.g_vec && o < p.CO && x0 + kWgTW <= p.W;
+    const bool g_in = x0 + kWgTW <= p.W;
     bf16x8 ga[kWgTH];
-    load_g<TG>(p, gp, o, y0, x0 + 8 * q, g_fast, ga);
+    load_g<TG, VEC>(p, gp, o, y0, x0 + 8 * q, g_in, ga);
     __syncthreads();  // the previous tile's readers are done with the LDS
 #pragma unroll
     for (int it = 0; it < (G::STAGE + kThreads - 1) / kThreads; ++it) {
@@ -1547,13 +1615,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
       if (task >= G::STAGE) break;
       const int c = task / (G::LH * G::CHUNKS), rest = task - c * (G::LH * G::CHUNKS);
       const int ly = rest / G::CHUNKS, ch = rest - ly * G::CHUNKS;
-      const u32x4 v = c < p.CI ? sv[it] : u32x4{0u, 0u, 0u, 0u};
+      u32x4 v = sv[it];
+      if (VEC && !x_in) {  // uniform
+        int tq = task;  // opaque: the chunk's columns are not kept from the loads
+        asm volatile("" : "+v"(tq));
+        const int shift = chunk_shift(x0 - 8 + 8 * (tq % G::CHUNKS), p.W);
+        if (shift) v = edge_chunk<false>(v, shift);
+      }
+      if (c >= p.CI) v = u32x4{0u, 0u, 0u, 0u};
       *reinterpret_cast<u32x4*>(xs + c * G::PLS + ly * G::LWP + 8 * ch) = v;
     }
     __syncthreads();
     // lane window: channel l16, columns 32 ks + 8q + {0..23} of every LDS row
     wg_rows<K, 0>(acc, ga, xs + l16 * G::PLS + 8 * q);
-    load_g<TG>(p, gp, o, y0, x0 + 32 + 8 * q, g_fast, ga);
+    load_g<TG, VEC>(p, gp, o, y0, x0 + 32 + 8 * q, g_in, ga);
     wg_rows<K, 0>(acc, ga, xs + l16 * G::PLS + 32 + 8 * q);
   }
   // D[o = wave*16 + 4q + j][ci = l16]
@@ -1634,7 +1709,7 @@ hipError_t conv_vr_go(const BankParams& pin, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int K, int OT, int PT, int CG, int NW, bool ADJ, typename TS, bool OB>
+template <int K, int OT, int PT, int CG, int NW, bool ADJ, typename TS, bool OB, bool VEC = true>
 hipError_t conv_go(const BankParams& pin, hipStream_t s) {
   using G = ConvGeom<K, OT, PT, CG, NW>;
   BankParams p = pin;
@@ -1654,7 +1729,7 @@ hipError_t conv_go(const BankParams& pin, hipStream_t s) {
     if (dev_cached != dev) {
       const void* kern;
       if constexpr (RING)
-        kern = reinterpret_cast<const void*>(k_bank_conv_ring<K, OT, PT, CG, ADJ, TS, OB>);
+        kern = reinterpret_cast<const void*>(k_bank_conv_ring<K, OT, PT, CG, ADJ, TS, OB, VEC>);
       else
         kern = reinterpret_cast<const void*>(k_bank_conv<K, OT, PT, CG, NW, ADJ, TS, OB>);
       e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
@@ -1672,7 +1747,7 @@ hipError_t conv_go(const BankParams& pin, hipStream_t s) {
   if constexpr (RING) {
     if (!plan_segments(p, grid)) return hipSuccess;
     const int64_t g = p.n_segs < grid ? p.n_segs : grid;
-    hipLaunchKernelGGL((k_bank_conv_ring<K, OT, PT, CG, ADJ, TS, OB>), dim3(static_cast<uint32_t>(g)),
+    hipLaunchKernelGGL((k_bank_conv_ring<K, OT, PT, CG, ADJ, TS, OB, VEC>), dim3(static_cast<uint32_t>(g)),
                        dim3(G::THREADS), lds, s, p);
     return hipGetLastError();
   }
@@ -1685,7 +1760,7 @@ hipError_t conv_go(const BankParams& pin, hipStream_t s) {
   }
 }
 
-template <int K, int CG>
+template <int K, int CG, bool WHOLE>
 hipError_t conv_ws_go(const BankParams& pin, hipStream_t s) {
   using WG = WsGeom<K, CG>;
   using G = typename WG::G;
@@ -1703,7 +1778,7 @@ hipError_t conv_ws_go(const BankParams& pin, hipStream_t s) {
   {
     std::lock_guard<std::mutex> lk(mu);
     if (dev_cached != dev) {
-      auto kern = k_bank_conv_ws<K, CG>;
+      auto kern = k_bank_conv_ws<K, CG, WHOLE>;
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                               static_cast<int>(lds));
       if (e != hipSuccess) return e;
@@ -1719,7 +1794,7 @@ hipError_t conv_ws_go(const BankParams& pin, hipStream_t s) {
   }
   const int64_t g = p.n_tiles < grid ? p.n_tiles : grid;
   if (g <= 0) return hipSuccess;
-  hipLaunchKernelGGL((k_bank_conv_ws<K, CG>), dim3(static_cast<uint32_t>(g)), dim3(threads), lds, s, p);
+  hipLaunchKernelGGL((k_bank_conv_ws<K, CG, WHOLE>), dim3(static_cast<uint32_t>(g)), dim3(threads), lds, s, p);
   return hipGetLastError();
 }
 
@@ -1736,6 +1811,8 @@ hipError_t conv_wide_go(const BankParams& p, hipStream_t s) {
 
 template <int K, bool ADJ, typename TS, bool OB>
 hipError_t conv_by_shape(const BankParams& p, int ot, int cg, hipStream_t s) {
+  // fewer than 8 columns: one shape that takes any channel counts
+  if (!p.s_vec) return conv_go<K, 1, 4, 8, 8, ADJ, TS, OB, false>(p, s);
   // instantiated (OT, CG) pairs, eight waves; 64-pixel tile rows (PT = 4),
   // 128 for 64 outputs from 9..16 inputs, where two source tiles of that
   // width still fit beside the weights; the adjoint's outputs are the
@@ -1745,7 +1822,7 @@ hipError_t conv_by_shape(const BankParams& p, int ot, int cg, hipStream_t s) {
       // BF16 outputs: the wave-specialised kernel (measured 4-5% faster at
       // K = 5); FP32 outputs: the eight-wave kernel on 4 x 128 tiles
       // (the specialised one measured slower there)
-      if constexpr (OB) return conv_ws_go<K, 2>(p, s);
+      if constexpr (OB) return p.W % 8 == 0 ? conv_ws_go<K, 2, true>(p, s) : conv_ws_go<K, 2, false>(p, s);
       return conv_go<K, 4, 8, 2, 8, ADJ, TS, OB>(p, s);
     }
     if (ot == 4 && cg == 1) return conv_go<K, 4, 4, 1, 8, ADJ, TS, OB>(p, s);
@@ -1783,11 +1860,12 @@ hipError_t conv_by_k(const BankParams& p, int K, int ot, int cg, hipStream_t s) 
 
 // output-channel tiles per work-group and channel groups of 8 for a map
 // with ci source and co output channels
-bool conv_shape(int64_t ci, int64_t co, int k, int* ot, int* cg) {
+bool conv_shape(int64_t ci, int64_t co, int64_t w, int k, int* ot, int* cg) {
   const int64_t g8 = (ci + 7) / 8;
   if (g8 > 8) return false;
   *cg = g8 <= 1 ? 1 : (g8 <= 2 ? 2 : (g8 <= 4 ? 4 : 8));
   *ot = co <= 16 ? 1 : (co <= 32 ? 2 : 4);
+  if (w < 8) *ot = 1;
   // keep weights + source tile within LDS
   if (*cg == 8 && *ot == 4) *ot = 2;
   if (*cg == 8 && k == 5) *ot = 1;
@@ -1818,7 +1896,7 @@ f2d_status bank_forward_bf16(const Problem& pr, const f2d_tensor* outs, hipStrea
   const f2d_tensor& im = pr.image;
   const f2d_tensor& out = outs[0];
   int ot, cg;
-  if (!conv_shape(im.c, pr.c_out, pr.k, &ot, &cg))
+  if (!conv_shape(im.c, pr.c_out, im.w, pr.k, &ot, &cg))
     return fail(F2D_EUNSUPPORTED, "bf16 banks: at most 64 input channels");
   if (pr.k != 1 && pr.k != 3 && pr.k != 5) return fail(F2D_EUNSUPPORTED, "bf16 banks: k in {1, 3, 5}");
   BankParams p;
@@ -1827,13 +1905,12 @@ f2d_status bank_forward_bf16(const Problem& pr, const f2d_tensor* outs, hipStrea
   p.s_sn = im.stride_n;
   p.s_sc = im.stride_c;
   p.s_sh = im.stride_h;
-  p.s_vec = row_aligned(im, 16) && im.w % 8 == 0 ? 1 : 0;
+  p.s_vec = im.w >= 8 ? 1 : 0;
   p.s_plan32 = p.s_vec && plan32_fits(im, im.c) ? 1 : 0;
   p.dst = out.data;
   p.d_sn = out.stride_n;
   p.d_sc = out.stride_c;
   p.d_sh = out.stride_h;
-  p.d_vec = row_aligned(out, out.dtype == F2D_BF16 ? 8 : 16) ? 1 : 0;
   p.w = static_cast<const uint16_t*>(pr.filter.data);
   p.H = im.h;
   p.W = im.w;
@@ -1878,20 +1955,19 @@ f2d_status bank_backward_bf16(const Problem& pr, const f2d_tensor& gout, const f
   const bool g32 = gout.dtype == F2D_F32;
   if (grad_input && !empty) {
     int ot, cg;
-    if (!conv_shape(pr.c_out, im.c, pr.k, &ot, &cg)) return fail(F2D_EUNSUPPORTED, "bf16 bank backward shape");
+    if (!conv_shape(pr.c_out, im.c, im.w, pr.k, &ot, &cg)) return fail(F2D_EUNSUPPORTED, "bf16 bank backward shape");
     BankParams p;
     std::memset(&p, 0, sizeof(p));
     p.src = gout.data;
     p.s_sn = gout.stride_n;
     p.s_sc = gout.stride_c;
     p.s_sh = gout.stride_h;
-    p.s_vec = row_aligned(gout, 16) && im.w % 8 == 0 ? 1 : 0;
+    p.s_vec = im.w >= 8 ? 1 : 0;
     p.s_plan32 = p.s_vec && plan32_fits(gout, pr.c_out) ? 1 : 0;
     p.dst = grad_input->data;
     p.d_sn = grad_input->stride_n;
     p.d_sc = grad_input->stride_c;
     p.d_sh = grad_input->stride_h;
-    p.d_vec = row_aligned(*grad_input, 16) ? 1 : 0;
     p.w = static_cast<const uint16_t*>(pr.filter.data);
     const int64_t r = (pr.k - 1) / 2;
     p.H = im.h;
@@ -1952,24 +2028,23 @@ f2d_status bank_backward_bf16(const Problem& pr, const f2d_tensor& gout, const f
       w.CO = static_cast<int32_t>(pr.c_out);
       w.tiles_x = tx;
       w.tiles_y = ty;
-      w.x_vec = row_aligned(im, 16) ? 1 : 0;
-      w.g_vec = row_aligned(gout, g32 ? 32 : 16) ? 1 : 0;
       w.n_tiles = n_tiles;
       w.units = units;
       const dim3 grid(static_cast<uint32_t>(units)), block(kThreads);
+      auto launch = [&](auto k) {
+        constexpr int K = decltype(k)::value;
+        if (im.w >= 8) {
+          if (g32) hipLaunchKernelGGL((k_bank_wgrad<K, float, true>), grid, block, 0, s, w);
+          else hipLaunchKernelGGL((k_bank_wgrad<K, uint16_t, true>), grid, block, 0, s, w);
+        } else {
+          if (g32) hipLaunchKernelGGL((k_bank_wgrad<K, float, false>), grid, block, 0, s, w);
+          else hipLaunchKernelGGL((k_bank_wgrad<K, uint16_t, false>), grid, block, 0, s, w);
+        }
+      };
       switch (pr.k) {
-        case 1:
-          if (g32) hipLaunchKernelGGL((k_bank_wgrad<1, float>), grid, block, 0, s, w);
-          else hipLaunchKernelGGL((k_bank_wgrad<1, uint16_t>), grid, block, 0, s, w);
-          break;
-        case 3:
-          if (g32) hipLaunchKernelGGL((k_bank_wgrad<3, float>), grid, block, 0, s, w);
-          else hipLaunchKernelGGL((k_bank_wgrad<3, uint16_t>), grid, block, 0, s, w);
-          break;
-        default:
-          if (g32) hipLaunchKernelGGL((k_bank_wgrad<5, float>), grid, block, 0, s, w);
-          else hipLaunchKernelGGL((k_bank_wgrad<5, uint16_t>), grid, block, 0, s, w);
-          break;
+        case 1: launch(std::integral_constant<int, 1>{}); break;
+        case 3: launch(std::integral_constant<int, 3>{}); break;
+        default: launch(std::integral_constant<int, 5>{}); break;
       }
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return hip_status(e, "bf16 bank wgrad launch");

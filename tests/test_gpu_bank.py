@@ -432,3 +432,40 @@ def test_bank_full_size(gpu_lib, k):
           f"{e_gf2:.3e} (rounded, images 0 and 31, every entry), {e_gfu:.3e} (unrounded, image 0)", flush=True)
     assert e_gf <= 1e-5 and e_gf2 <= 1e-5
     assert e_gfu <= 1e-2
+
+
+@pytest.mark.parametrize("w", [4, 7, 8, 9, 12, 15, 57, 63, 65, 70, 127, 129])
+@pytest.mark.parametrize("cio", [(16, 64), (8, 16), (16, 40), (64, 16), (40, 20)])
+@pytest.mark.parametrize("k", [1, 3, 5])
+def test_odd_widths_and_offsets_are_bit_exact(gpu_lib, cio, w, k):
+    """Widths around the 8-column staging chunks (fewer than 8 columns, a
+    chunk across the row's end at every tile position) in rows that start at
+    odd addresses, through each kernel family; upstream gradients in BF16 and
+    FP32.  Integer operands: bit-exact."""
+    cin, cout = cio
+    h = 11
+    r = wl.rng(61, cin, cout, w, k)
+    wide = lambda c: r.integers(-4, 5, (2, c, h + 2, w + 3)).astype(np.float32)  # noqa: E731
+    cut = lambda t: t[:, :, 1:h + 1, 1:w + 1]  # noqa: E731
+    print(cio, w, k, flush=True)
+    xb, xv = bf(wide(cin))
+    fb, fv = bf(r.integers(-4, 5, (cout, cin, k, k)).astype(np.float32))
+    want = oracle.forward(cut(xv), fv, "bank")
+    assert_same(host(gpu_lib.forward(cut(xb), fb, mode="bank")), want)
+    yb = torch.full((2, cout, h + 2, w + 3), 7.0, device="cuda").bfloat16()
+    gpu_lib.forward(cut(xb), fb, mode="bank", outs=[cut(yb)])
+    rounded = torch.from_numpy(want).float().bfloat16()  # (integers: one rounding to nearest even)
+    assert torch.equal(cut(yb).cpu(), rounded)
+    keep = torch.full_like(yb, 7.0)
+    cut(keep).copy_(cut(yb))
+    assert torch.equal(yb, keep)
+    if cin > 16:
+        return
+    g = wide(cout)
+    gb, gv = bf(g)
+    want_i = oracle.grad_input(cut(gv), fv, (2, cin, h, w), "bank")
+    want_f = oracle.grad_filter(cut(xv), cut(gv), fv.shape, "bank")
+    for up in (gb, f32(g)):
+        gi, gf = gpu_lib.backward(cut(xb), fb, cut(up), mode="bank")
+        assert_same(host(gi), want_i)
+        assert_same(host(gf), want_f)
