@@ -4,7 +4,7 @@
 // pixel after another) with float taps: a 3x3 Laplacian sharpen that skips
 // out-of-image neighbours (Section 4.2.4), run on images enlarged by nearest-
 // neighbour upsampling (Section 4.2.3; the pipeline of Section 6.6), and a
-// weighted RGB -> gray sum (Section 4.2.5).  Two kernels cover them:
+// weighted RGB -> gray sum (Section 4.2.5).  Three kernels cover them:
 //
 //  k_u8_gather  one K x K filter (SHARED mode) on planar or interleaved 8-bit
 //               images, clamp-to-edge or zero borders, optionally through a
@@ -21,6 +21,7 @@
 //               of 8 + 2rC bytes.  Rows whose K source rows are the same as the
 //               previous row's (inside an upsampled block when s > 1) reuse
 //               the previous values and only store.
+//  k_u8_direct  the 3 x 3 filter into 8-bit outputs, upsampled by 1 to 4.
 //  k_u8_mix     per-pixel channel mixing (BANK mode with K = 1, e.g. the
 //               grayscale weights): up to 4 input and 4 output channels,
 //               planar or interleaved, four pixels per lane.
@@ -333,6 +334,373 @@ __global__ __launch_bounds__(kGThreads) void k_u8_gather(GatherParams p) {
   }
 }
 
+// ----------------------------------------------------- 3 x 3, 8-bit out --
+//
+// k_u8_direct: the paper's case (3 x 3 taps, 8-bit output, nearest upsample by
+// 1 to 4).  k_u8_gather expands every row in LDS and then converts and
+// multiplies each of an output's 9 bytes: 20 VALU and 14 scalar instructions
+// per output byte, which held the 4K x2 sharpen at 78 us where its traffic
+// takes 27.  Here a lane owns SPX neighbouring source pixels, loads each
+// source row's (SPX + 2)-pixel window once, straight to registers, and
+// produces the SPX * S output pixels of S output rows from the three windows
+// around it: byte positions are compile-time constants, so a source byte is
+// converted once for all its uses, equal outputs of the same source pixels are
+// computed once, and there is no LDS, no barrier and no index arithmetic per
+// output.  A wave walks down run_rows source rows of a 64 * SPX-pixel strip,
+// its loads two rows ahead.  4K x2: 35 us, 3.5 TB/s of the 4.7 that a copy
+// reaches.
+//
+// Whole-number taps (S <= 2; the paper's Laplacian) take 8-bit dot products:
+// the sums are integers below 2^24, exact in any order, so taps that meet the
+// same source byte are added first and four bytes go through one instruction.
+// Larger factors repeat outputs, and the float chain is no slower there.
+struct DirectParams {
+  const uint8_t* src;
+  int64_t s_sn, s_sc, s_sh;
+  uint8_t* dst;
+  int64_t d_sn, d_sc, d_sh;
+  const void* taps;  // 9 int32 or float
+  int64_t H, W;      // source image, pixels
+  int64_t q0, q1;    // source rows whose output rows are produced (S = 1: the band; output row q*S - row_off)
+  int64_t row_off;
+  int32_t zero, planes_c, run_rows;
+  int32_t strips, runs;
+  int64_t n_waves;
+};
+
+typedef uint32_t u32_a1 __attribute__((aligned(1)));
+typedef uint32_t u32x2_a1 __attribute__((ext_vector_type(2), aligned(1)));
+typedef uint32_t u32x4_a1 __attribute__((ext_vector_type(4), aligned(1)));
+
+// N words from / to any byte address
+template <int N>
+__device__ __forceinline__ void load_words(const uint8_t* a, uint32_t (&w)[N]) {
+  constexpr int N4 = N / 4 * 4, N2 = N4 + (N - N4) / 2 * 2;
+#pragma unroll
+  for (int i = 0; i < N4; i += 4) {
+    const u32x4_a1 t = *reinterpret_cast<const u32x4_a1*>(a + 4 * i);
+    w[i] = t[0];
+    w[i + 1] = t[1];
+    w[i + 2] = t[2];
+    w[i + 3] = t[3];
+  }
+  if constexpr (N2 > N4) {
+    const u32x2_a1 t = *reinterpret_cast<const u32x2_a1*>(a + 4 * N4);
+    w[N4] = t[0];
+    w[N4 + 1] = t[1];
+  }
+  if constexpr (N > N2) w[N2] = *reinterpret_cast<const u32_a1*>(a + 4 * N2);
+}
+template <int N>
+__device__ __forceinline__ void store_words(uint8_t* a, const uint32_t (&w)[N]) {
+  constexpr int N4 = N / 4 * 4, N2 = N4 + (N - N4) / 2 * 2;
+#pragma unroll
+  for (int i = 0; i < N4; i += 4)
+    *reinterpret_cast<u32x4_a1*>(a + 4 * i) = u32x4_a1{w[i], w[i + 1], w[i + 2], w[i + 3]};
+  if constexpr (N2 > N4) *reinterpret_cast<u32x2_a1*>(a + 4 * N4) = u32x2_a1{w[N4], w[N4 + 1]};
+  if constexpr (N > N2) *reinterpret_cast<u32_a1*>(a + 4 * N2) = w[N2];
+}
+
+// Source offset (-1, 0, 1) that tap t (0..2) of upsampled phase ph meets.
+template <int S>
+constexpr int phase_src(int ph, int t) {
+  const int x = ph + t - 1;
+  return x < 0 ? -1 : (x >= S ? 1 : 0);
+}
+
+template <int P, int S, int SPX>
+struct DirectGeom {
+  static constexpr int NE = SPX * S * P;             // output bytes of a lane and row
+  static constexpr int NB = (SPX + 2) * P;           // window bytes of a source row
+  static constexpr int NW = (NB + 3) / 4, NO = NE / 4;
+  static constexpr bool DOT = S <= 2;
+  static_assert(NE % 4 == 0, "whole words");
+  // window byte of the source pixel at offset d from that of element e
+  static constexpr int byte_of(int e, int d) { return (e / P / S + d + 1) * P + e % P; }
+};
+
+// One output row (phase r) of the lane from the windows of the source rows
+// above, at and below it, in the order of the definition (taps u, then v).
+template <int P, int S, int SPX, bool TF>
+__device__ __forceinline__ void direct_row(const uint32_t (&w)[3][DirectGeom<P, S, SPX>::NW],
+                                           const typename std::conditional<TF, float, uint32_t>::type (&tap)[9],
+                                           int r, uint32_t (&o)[DirectGeom<P, S, SPX>::NO]) {
+  using G = DirectGeom<P, S, SPX>;
+  using Acc = typename std::conditional<TF, float, uint32_t>::type;
+#pragma unroll
+  for (int i = 0; i < G::NO; ++i) {
+    uint32_t word = 0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int e = 4 * i + b;
+      Acc acc = Acc(0);
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+#pragma unroll
+        for (int v = 0; v < 3; ++v) {
+          const int at = G::byte_of(e, phase_src<S>(e / P % S, v));
+          const uint32_t byte = (w[1 + phase_src<S>(r, u)][at / 4] >> (8 * (at % 4))) & 0xffu;
+          if constexpr (TF)
+            acc = __builtin_fmaf(tap[3 * u + v], static_cast<float>(byte), acc);
+          else
+            acc += byte * tap[3 * u + v];
+        }
+      uint32_t q;
+      if constexpr (TF) {
+        q = static_cast<uint32_t>(__builtin_rintf(__builtin_amdgcn_fmed3f(acc, 0.0f, 255.0f)));
+      } else {
+        const int32_t x = static_cast<int32_t>(acc);
+        q = static_cast<uint32_t>(x < 0 ? 0 : (x > 255 ? 255 : x));
+      }
+      word |= q << (8 * b);
+    }
+    o[i] = word;
+  }
+}
+
+// Tap words of the dot products: source row d (-1..1) of output phase r meets
+// the sum of the tap rows u with phase_src(r, u) = d; within it, byte at of an
+// element's window the sum of the taps v that meet it.
+template <int P, int S>
+struct DirectTaps {
+  // [row phase][source row][column phase][byte alignment][word]
+  uint32_t t[S][3][S][4][3];
+  int32_t bias;
+  bool fits;
+  __device__ __forceinline__ void set(const int32_t (&tap)[9]) {
+    fits = true;
+    bias = 0;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) bias += 128 * tap[i];
+#pragma unroll
+    for (int r = 0; r < S; ++r)
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int c = 0; c < S; ++c) {
+          int32_t sum[3];
+#pragma unroll
+          for (int x = 0; x < 3; ++x) {
+            sum[x] = 0;
+#pragma unroll
+            for (int u = 0; u < 3; ++u)
+#pragma unroll
+              for (int v = 0; v < 3; ++v)
+                if (phase_src<S>(r, u) == d - 1 && phase_src<S>(c, v) == x - 1) sum[x] += tap[3 * u + v];
+            fits = fits && sum[x] >= -128 && sum[x] <= 127;
+          }
+#pragma unroll
+          for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+              uint32_t word = 0;
+#pragma unroll
+              for (int x = 0; x < 3; ++x)
+                if ((a + x * P) / 4 == q) word |= (static_cast<uint32_t>(sum[x]) & 0xffu) << (8 * ((a + x * P) % 4));
+              t[r][d][c][a][q] = __builtin_amdgcn_readfirstlane(word);
+            }
+        }
+  }
+};
+
+// direct_row through the dot products; the windows hold the bytes minus 128.
+template <int P, int S, int SPX>
+__device__ __forceinline__ void direct_row_dot(const uint32_t (&w)[3][DirectGeom<P, S, SPX>::NW],
+                                               const DirectTaps<P, S>& tp, int r,
+                                               uint32_t (&o)[DirectGeom<P, S, SPX>::NO]) {
+  using G = DirectGeom<P, S, SPX>;
+#pragma unroll
+  for (int i = 0; i < G::NO; ++i) {
+    uint32_t word = 0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int e = 4 * i + b, c = e / P % S, at = G::byte_of(e, -1);
+      int32_t acc = tp.bias;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        bool row = false;  // some tap row meets this source row
+#pragma unroll
+        for (int u = 0; u < 3; ++u) row = row || phase_src<S>(r, u) == d - 1;
+        if (!row) continue;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          bool word_used = false;
+#pragma unroll
+          for (int v = 0; v < 3; ++v) word_used = word_used || (at % 4 + (phase_src<S>(c, v) + 1) * P) / 4 == q;
+          if (word_used)
+            acc = __builtin_amdgcn_sdot4(static_cast<int>(w[d][at / 4 + q]),
+                                         static_cast<int>(tp.t[r][d][c][at % 4][q]), acc, false);
+        }
+      }
+      word |= static_cast<uint32_t>(acc < 0 ? 0 : (acc > 255 ? 255 : acc)) << (8 * b);
+    }
+    o[i] = word;
+  }
+}
+
+template <int P, int S, int SPX, bool TF>
+__global__ __launch_bounds__(kGThreads) void k_u8_direct(DirectParams p) {
+  using G = DirectGeom<P, S, SPX>;
+  using Acc = typename std::conditional<TF, float, uint32_t>::type;
+  const int lane = threadIdx.x % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const int64_t item = xcd_remap(blockIdx.x, gridDim.x) * (kGThreads / 64) + wave;
+  if (item >= p.n_waves) return;  // no barriers in this kernel
+  const uint32_t it = static_cast<uint32_t>(item);
+  const uint32_t rest = it / static_cast<uint32_t>(p.strips);
+  const uint32_t strip = it - rest * p.strips;
+  const uint32_t plane = rest / static_cast<uint32_t>(p.runs);
+  const int64_t qa = p.q0 + static_cast<int64_t>(rest - plane * p.runs) * p.run_rows;
+  const int64_t qb = qa + p.run_rows < p.q1 ? qa + p.run_rows : p.q1;
+  const uint32_t n = plane / static_cast<uint32_t>(p.planes_c), c = plane - n * p.planes_c;
+  const uint8_t* sp = p.src + n * p.s_sn + c * p.s_sc;
+  uint8_t* dp = p.dst + n * p.d_sn + c * p.d_sc;
+  const int64_t px = (static_cast<int64_t>(strip) * 64 + lane) * SPX;  // this lane's first source pixel
+  if (px >= p.W) return;
+
+  Acc tap[9];
+#pragma unroll
+  for (int i = 0; i < 9; ++i) tap[i] = static_cast<const Acc*>(p.taps)[i];
+  bool dot = G::DOT;
+  DirectTaps<P, G::DOT ? S : 1> tp;
+  if constexpr (G::DOT) {
+    int32_t ti[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      if constexpr (TF) {
+        const float t = tap[i] >= -128.0f && tap[i] <= 127.0f ? tap[i] : 0.5f;  // (also NaN)
+        ti[i] = static_cast<int32_t>(t);
+        dot = dot && static_cast<float>(ti[i]) == t;
+      } else {
+        ti[i] = static_cast<int32_t>(tap[i]);
+        dot = dot && ti[i] >= -128 && ti[i] <= 127;
+      }
+    }
+    if (!dot) {
+#pragma unroll
+      for (int i = 0; i < 9; ++i) ti[i] = 0;
+    }
+    tp.set(ti);
+    dot = dot && tp.fits;
+  }
+  dot = __builtin_amdgcn_readfirstlane(dot) != 0;
+  const uint32_t flip = dot ? 0x80808080u : 0u;
+
+  // the window of source row q: clamped to the image, or zeros outside it
+  auto clamp_row = [&](int64_t q) { return q < 0 ? 0 : (q >= p.H ? p.H - 1 : q); };
+  auto finish = [&](int64_t q, uint32_t (&w)[G::NW]) {
+    const uint32_t keep = p.zero && (q < 0 || q >= p.H) ? 0u : 0xffffffffu;  // uniform
+#pragma unroll
+    for (int i = 0; i < G::NW; ++i) w[i] = (w[i] & keep) ^ flip;
+  };
+  // every byte that load_words reads lies in the row, every pixel in the
+  // image, for each lane of the wave (uniform)
+  const bool mine = px >= 1 && (px - 1) * P + 4 * G::NW <= p.W * P && px + SPX <= p.W;
+  const bool inside = __ballot(!mine) == 0;
+  const uint8_t* wa = sp + (px - 1) * P;
+  auto load = [&](int64_t q, uint32_t (&w)[G::NW]) { load_words<G::NW>(wa + clamp_row(q) * p.s_sh, w); };
+  // at the ends of the rows: byte by byte, packed when the row is needed
+  auto load_bytes = [&](int64_t q, uint32_t (&v)[G::NB]) {
+    const uint8_t* row = sp + clamp_row(q) * p.s_sh;
+#pragma unroll
+    for (int x = 0; x < SPX + 2; ++x) {
+      const int64_t g = px + x - 1, gc = g < 0 ? 0 : (g >= p.W ? p.W - 1 : g);
+#pragma unroll
+      for (int ch = 0; ch < P; ++ch) v[x * P + ch] = row[gc * P + ch];
+    }
+  };
+  auto pack = [&](const uint32_t (&v)[G::NB], uint32_t (&w)[G::NW]) {
+#pragma unroll
+    for (int i = 0; i < G::NW; ++i) w[i] = 0;
+#pragma unroll
+    for (int x = 0; x < SPX + 2; ++x) {
+      const int64_t g = px + x - 1;
+      const bool out = p.zero && (g < 0 || g >= p.W);
+#pragma unroll
+      for (int ch = 0; ch < P; ++ch) {
+        const int at = x * P + ch;
+        w[at / 4] |= (out ? 0u : v[at]) << (8 * (at % 4));
+      }
+    }
+  };
+  auto row_out = [&](const uint32_t (&w)[3][G::NW], int r, uint32_t (&o)[G::NO]) {
+    if constexpr (G::DOT) {
+      if (dot) {  // uniform
+        direct_row_dot<P, S, SPX>(w, tp, r, o);
+        return;
+      }
+    }
+    direct_row<P, S, SPX, TF>(w, tap, r, o);
+  };
+
+  uint32_t w[3][G::NW], nx[G::NW];
+  if (inside) {
+    load(qa - 1, w[0]);
+    load(qa, w[1]);
+    load(qa + 1, w[2]);
+    load(qa + 2, nx);
+    finish(qa - 1, w[0]);
+    finish(qa, w[1]);
+    finish(qa + 1, w[2]);
+    uint8_t* d = dp + (qa * S - p.row_off) * p.d_sh + px * S * P;
+    for (int64_t q = qa; q < qb; ++q) {
+      uint32_t n2[G::NW];
+      load(q + 3, n2);
+#pragma unroll
+      for (int r = 0; r < S; ++r) {
+        uint32_t o[G::NO];
+        row_out(w, r, o);
+        store_words<G::NO>(d, o);
+        d += p.d_sh;
+      }
+      finish(q + 2, nx);
+#pragma unroll
+      for (int i = 0; i < G::NW; ++i) {
+        w[0][i] = w[1][i];
+        w[1][i] = w[2][i];
+        w[2][i] = nx[i];
+        nx[i] = n2[i];
+      }
+    }
+  } else {
+    uint32_t v[G::NB];
+    load_bytes(qa - 1, v);
+    pack(v, w[0]);
+    load_bytes(qa, v);
+    pack(v, w[1]);
+    load_bytes(qa + 1, v);
+    pack(v, w[2]);
+    finish(qa - 1, w[0]);
+    finish(qa, w[1]);
+    finish(qa + 1, w[2]);
+    const int64_t bytes = (p.W - px) * S * P;  // of this lane inside the image
+    for (int64_t q = qa; q < qb; ++q) {
+      load_bytes(q + 2, v);
+#pragma unroll
+      for (int r = 0; r < S; ++r) {
+        uint32_t o[G::NO];
+        row_out(w, r, o);
+        uint8_t* d = dp + (q * S + r - p.row_off) * p.d_sh + px * S * P;
+        if (bytes >= G::NE) {
+          store_words<G::NO>(d, o);
+        } else {
+#pragma unroll
+          for (int e = 0; e < G::NE; ++e)
+            if (e < bytes) d[e] = static_cast<uint8_t>(o[e / 4] >> (8 * (e % 4)));
+        }
+      }
+      pack(v, nx);
+      finish(q + 2, nx);
+#pragma unroll
+      for (int i = 0; i < G::NW; ++i) {
+        w[0][i] = w[1][i];
+        w[1][i] = w[2][i];
+        w[2][i] = nx[i];
+      }
+    }
+  }
+}
+
 // ------------------------------------------------------------- channel mix --
 
 struct MixParams {
@@ -513,6 +881,45 @@ hipError_t launch_gather_k(const GatherParams& g, int P, bool tf, int out, int e
 
 int out_kind(int32_t dtype) { return dtype == F2D_U8 ? kOutU8 : (dtype == F2D_F32 ? kOutF32 : kOutI32); }
 
+template <int P, int S, int SPX>
+hipError_t launch_direct_one(DirectParams d, int64_t planes, bool tf, hipStream_t s) {
+  d.strips = static_cast<int32_t>((d.W + 64 * SPX - 1) / (64 * SPX));
+  const int64_t rows = d.q1 - d.q0;
+  // 8 source rows per wave (two halo rows each), fewer where that leaves the
+  // GPU's 8192 wave slots half empty
+  int64_t run = 8;
+  while (run > 2 && planes * d.strips * ((rows + run - 1) / run) < 4096) run /= 2;
+  d.run_rows = static_cast<int32_t>(run);
+  d.runs = static_cast<int32_t>((rows + run - 1) / run);
+  d.n_waves = planes * d.strips * d.runs;
+  const int64_t blocks = (d.n_waves + kGThreads / 64 - 1) / (kGThreads / 64);
+  if (blocks <= 0) return hipSuccess;
+  const dim3 grid(static_cast<uint32_t>(blocks)), block(kGThreads);
+  if (tf) hipLaunchKernelGGL((k_u8_direct<P, S, SPX, true>), grid, block, 0, s, d);
+  else hipLaunchKernelGGL((k_u8_direct<P, S, SPX, false>), grid, block, 0, s, d);
+  return hipGetLastError();
+}
+
+// Source pixels per lane: whole words of output, and strips narrow enough that
+// few of a row's waves hold its ends (those load by bytes: 16 planar pixels per
+// lane at x1 took 35 us on three 4K planes, 8 take 25, 4 take 30).
+hipError_t launch_direct(const DirectParams& d, int64_t planes, int P, int scale, bool tf, hipStream_t s) {
+  switch (P * 8 + scale) {
+    case 1 * 8 + 1: return launch_direct_one<1, 1, 8>(d, planes, tf, s);
+    case 1 * 8 + 2: return launch_direct_one<1, 2, 4>(d, planes, tf, s);
+    case 1 * 8 + 3: return launch_direct_one<1, 3, 4>(d, planes, tf, s);
+    case 1 * 8 + 4: return launch_direct_one<1, 4, 4>(d, planes, tf, s);
+    case 3 * 8 + 1: return launch_direct_one<3, 1, 4>(d, planes, tf, s);
+    case 3 * 8 + 2: return launch_direct_one<3, 2, 4>(d, planes, tf, s);
+    case 3 * 8 + 3: return launch_direct_one<3, 3, 4>(d, planes, tf, s);
+    case 3 * 8 + 4: return launch_direct_one<3, 4, 1>(d, planes, tf, s);
+    case 4 * 8 + 1: return launch_direct_one<4, 1, 4>(d, planes, tf, s);
+    case 4 * 8 + 2: return launch_direct_one<4, 2, 2>(d, planes, tf, s);
+    case 4 * 8 + 3: return launch_direct_one<4, 3, 4>(d, planes, tf, s);
+    default: return launch_direct_one<4, 4, 1>(d, planes, tf, s);
+  }
+}
+
 // SHARED filter on an 8-bit image, optional nearest upsample by `scale`.
 f2d_status gather_forward(const Problem& pr, const f2d_tensor& out, int32_t scale, hipStream_t s) {
   const f2d_tensor& im = pr.image;
@@ -550,6 +957,32 @@ f2d_status gather_forward(const Problem& pr, const f2d_tensor& out, int32_t scal
   const int64_t L = g.Wout * P;
   if (L > (int64_t{1} << 30) || g.Hout > (int64_t{1} << 30))
     return fail(F2D_EUNSUPPORTED, "u8 filter: output rows of at most 2^30 elements and 2^30 rows");
+  // 3 x 3 into bytes, factors to 4: k_u8_direct (4K interleaved, gather /
+  // direct: x1 36 / 27 us, x2 76 / 35, x3 134 / 75, x4 199 / 113).  Larger
+  // factors are bound by their stores either way and stay with the gather.
+  if (pr.k == 3 && ok_out == kOutU8 && scale <= 4) {
+    DirectParams d;
+    std::memset(&d, 0, sizeof(d));
+    d.src = g.src;
+    d.s_sn = g.s_sn;
+    d.s_sc = g.s_sc;
+    d.s_sh = g.s_sh;
+    d.dst = static_cast<uint8_t*>(out.data);
+    d.d_sn = g.d_sn;
+    d.d_sc = g.d_sc;
+    d.d_sh = g.d_sh;
+    d.taps = g.taps;
+    d.H = g.H;
+    d.W = g.W;
+    d.q0 = scale == 1 ? pr.row_begin : 0;
+    d.q1 = scale == 1 ? pr.row_end : im.h;
+    d.row_off = scale == 1 ? pr.row_begin : 0;
+    d.zero = g.zero;
+    d.planes_c = g.planes_c;
+    const int64_t planes = im.n * g.planes_c;
+    if (planes * ((im.h + 1) / 2) * ((im.w + 63) / 64) < (int64_t{1} << 31))  // wave numbers fit in 32 bits
+      return hip_status(launch_direct(d, planes, P, scale, tf, s), "u8 3x3 filter launch");
+  }
   // Tile height: 16 rows without upsampling; with it, about 8 source rows
   // per tile (rows inside an upsampled block repeat, so the work per tile is
   // set by its source rows), at most 512 rows.  LDS holds the tile's source

@@ -232,3 +232,59 @@ def test_grayscale_8k_full_size(gpu_lib):
     for (y0, y1) in [(0, 8), (2000, 2016), (4312, 4320)]:
         want = expect(planar_of(x[y0:y1]), GRAY, "clamp", "u8", mode="bank")
         assert np.array_equal(y[:, :, y0:y1].cpu().numpy(), want)
+
+
+# taps of the direct 3 x 3 kernel: whole numbers (dot products), whole numbers
+# whose sums over one source pixel leave a signed byte, fractions, large ones
+DIRECT_TAPS = {
+    "laplacian": LAP,
+    "bytes": np.array([[127, -128, 0], [1, -1, 127], [-128, 64, -64]], np.float32),
+    "beyond": np.array([[100, 100, -3], [100, 100, 5], [-90, 0, -100]], np.float32),
+    "fractions": np.array([[0.1, -0.25, 0.3], [1.5, 0.7, -0.6], [0.01, -0.2, 0.9]], np.float32),
+    "large": np.array([[300, -1000, 7], [0, 512, 200], [-129, 128, 40]], np.float32),
+}
+
+
+@pytest.mark.parametrize("taps", sorted(DIRECT_TAPS))
+@pytest.mark.parametrize("scale", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("c", [1, 3, 4])
+def test_direct_3x3_at_its_edges(gpu_lib, c, scale, taps):
+    """Widths around a lane's pixels and a wave's strip (one pixel; less than a
+    window; one strip exactly, one more, one less), heights around a wave's
+    rows, planar (c = 1 channel each) and interleaved, both borders, float and
+    int32 taps; rows at odd addresses."""
+    f = DIRECT_TAPS[taps]
+    widths = [1, 2, 3, 5, 9, 63, 64, 65, 128, 255, 256, 257, 511, 512, 513]
+    heights = [1, 2, 3, 8, 9]
+    for i, w in enumerate(widths):
+        if w == 1 and c > 1:
+            continue  # a one-pixel row has no column stride to tell its layout by
+        h = heights[i % len(heights)]
+        r = wl.rng(91, c, scale, w)
+        big = r.integers(0, 256, (2, h + 1, w + 1, c), dtype=np.uint8)
+        if c == 1:  # two planes per image
+            big = r.integers(0, 256, (2, 2, h + 1, w + 1), dtype=np.uint8)
+            x, xd = big[:, :, 1:, 1:], dev(big)[:, :, 1:, 1:]
+        else:
+            x = np.ascontiguousarray(big[:, 1:, 1:].transpose(0, 3, 1, 2))
+            xd = torch.from_numpy(big).cuda()[:, 1:, 1:].permute(0, 3, 1, 2)
+        for border in ("zero", "clamp"):
+            for tf in (f, f.astype(np.int32)):
+                print(c, scale, taps, w, h, border, tf.dtype, flush=True)
+                if not np.array_equal(tf, f):
+                    continue
+                y = gpu_lib.upsample_forward(xd, dev(tf), scale, out_dtype=torch.uint8, border=border)
+                assert np.array_equal(y.cpu().numpy(), expect(x, tf, border, "u8", scale=scale))
+
+
+@pytest.mark.parametrize("taps", ["laplacian", "fractions"])
+def test_direct_3x3_bands(gpu_lib, taps):
+    """Row bands concatenate to the whole image, bytes equal."""
+    f = dev(DIRECT_TAPS[taps])
+    x = hwc_dev(wl.rng(92).integers(0, 256, (1, 41, 300, 3), dtype=np.uint8))
+    whole = gpu_lib.forward(x, f, border="zero", out_dtype=torch.uint8)
+    parts = []
+    for y0, y1 in [(0, 1), (1, 9), (9, 30), (30, 41)]:
+        lo, hi = max(0, y0 - 1), min(41, y1 + 1)
+        parts.append(gpu_lib.forward(x[:, :, lo:hi], f, border="zero", out_dtype=torch.uint8, rows=(y0 - lo, y1 - lo)))
+    assert torch.equal(torch.cat(parts, dim=2), whole)
