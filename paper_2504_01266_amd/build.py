@@ -1,4 +1,6 @@
-"""Build libfilter2d.so (all HIP sources under csrc/) for gfx950 with hipcc.
+"""Build libfilter2d.so (all HIP sources under csrc/) for gfx950 with hipcc,
+and the Python extension module _hostcall (csrc/hostcall.cpp) with the host
+compiler.
 
 Each source is compiled to an object in parallel, then the objects are linked
 into a shared library next to this file.  Packed FP32 instructions are
@@ -9,6 +11,7 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -16,6 +19,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libfilter2d.so")
+HOSTCALL = os.path.join(HERE, "_hostcall.so")
 ARCH = os.environ.get("F2D_OFFLOAD_ARCH", "gfx950")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -41,12 +45,34 @@ def _compile(src, verbose):
     return obj
 
 
+def _build_hostcall(verbose):
+    """The marshalling module: host code only, against torch's own headers
+    (its libraries are in the process once torch is imported)."""
+    import torch
+
+    base = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", INCLUDE,
+           "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(base, "include"),
+           "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           os.path.join(CSRC, "hostcall.cpp"), "-L" + os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu",
+           "-lc10", "-o", HOSTCALL + ".tmp"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"hostcall.cpp failed to compile:\n{r.stdout}\n{r.stderr}")
+    os.replace(HOSTCALL + ".tmp", HOSTCALL)
+
+
 def build(verbose=False, jobs=None):
     os.makedirs(BUILD_DIR, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
     jobs = jobs or min(len(srcs), os.cpu_count() or 4, 16)
-    with cf.ThreadPoolExecutor(jobs) as ex:
+    with cf.ThreadPoolExecutor(jobs + 1) as ex:
+        host = ex.submit(_build_hostcall, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), srcs))
+        host.result()
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", LIB + ".tmp"]
     if verbose:
         print(" ".join(cmd), flush=True)
