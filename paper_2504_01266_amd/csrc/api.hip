@@ -169,14 +169,6 @@ f2d_status check_tensor(const f2d_tensor* t, const char* name, bool is_output) {
 
 size_t dtype_size(int32_t dt) { return dt == F2D_U8 ? 1 : (dt == F2D_BF16 ? 2 : 4); }
 
-bool row_aligned(const f2d_tensor& t, size_t bytes) {
-  const size_t es = dtype_size(t.dtype);
-  const uintptr_t a = reinterpret_cast<uintptr_t>(t.data);
-  auto ok_stride = [&](int64_t s, int64_t extent) { return extent <= 1 || (s * es) % bytes == 0; };
-  return a % bytes == 0 && ok_stride(t.stride_h, t.h) && ok_stride(t.stride_c, t.c) &&
-         ok_stride(t.stride_n, t.n);
-}
-
 f2d_status check_common(const f2d_tensor* image, const f2d_filter* filter, const f2d_opts* opts,
                         Problem* pr) {
   if (!opts) return fail(F2D_EINVAL, "opts is NULL");

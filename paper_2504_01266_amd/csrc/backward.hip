@@ -238,7 +238,6 @@ f2d_status run_backward(const Problem& pr, const f2d_tensor* grad_outs, int32_t 
     e.out_sc = grad_input->stride_c;
     e.out_sh = grad_input->stride_h;
     e.planes = im.n * im.c;
-    p.flags = row_aligned(*grad_input, 16) ? kDstVec : 0;
 
     const bool templ = K <= 9;
     const TileShape ts = f32_tile(templ ? 1 : -1);
@@ -335,9 +334,6 @@ f2d_status run_backward(const Problem& pr, const f2d_tensor* grad_outs, int32_t 
         q.g_sc[t] = g.stride_c;
         q.g_sh[t] = g.stride_h;
       }
-      bool gvec = true;
-      for (int32_t j = 0; j < n_grad_outs; ++j) gvec = gvec && row_aligned(grad_outs[j], 16);
-      q.flags = gvec ? kDstVec : 0;
       q.partial = partial;
       q.H = im.h;
       q.W = im.w;

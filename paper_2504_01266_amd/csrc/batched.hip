@@ -112,12 +112,10 @@ __global__ __launch_bounds__(kThreads) void k_batched_f32(const f2d_batch_item* 
     accumulate<K, 1, PX, PY>(lds, tap, acc);
 
     const auto dp = global_ptr(static_cast<float*>(it.out)) + c * it.out_stride_c;
-    const bool vec = (reinterpret_cast<uintptr_t>(it.out) % 16 == 0) && (it.out_stride_h % 4 == 0) &&
-                     (it.out_stride_c % 4 == 0);
 #pragma unroll
     for (int jy = 0; jy < PY; ++jy) {
       const int64_t oy = oy0 + ty * PY + jy;
-      if (oy < it.h) store_row<PX>(dp + oy * it.out_stride_h, ox0 + tx * PX, it.w, vec, acc[0][jy]);
+      if (oy < it.h) store_row<PX>(dp + oy * it.out_stride_h, ox0 + tx * PX, it.w, acc[0][jy]);
     }
     __syncthreads();  // the next tile overwrites the LDS tile
   }
@@ -364,13 +362,11 @@ __global__ __launch_bounds__(kThreads) void k_batched_pipe(const f2d_batch_item*
     __syncthreads();
     accumulate_off<K, PX, PY>(lds, tap, acc);
     const auto dp = global_ptr(static_cast<float*>(it.out)) + cc.c * it.out_stride_c;
-    const bool vec = (reinterpret_cast<uintptr_t>(it.out) % 16 == 0) && (it.out_stride_h % 4 == 0) &&
-                     (it.out_stride_c % 4 == 0);
     const int64_t oy0 = static_cast<int64_t>(cc.ty) * G::TH, ox0 = static_cast<int64_t>(cc.tx) * G::TW;
 #pragma unroll
     for (int jy = 0; jy < PY; ++jy) {
       const int64_t oy = oy0 + ty * PY + jy;
-      if (oy < it.h) store_row<PX>(dp + oy * it.out_stride_h, ox0 + tx * PX, it.w, vec, acc[jy]);
+      if (oy < it.h) store_row<PX>(dp + oy * it.out_stride_h, ox0 + tx * PX, it.w, acc[jy]);
     }
     if (t + 1 < t1) {
       cursor_step<G::TH, G::TW>(items, prefix, n_items, cc);

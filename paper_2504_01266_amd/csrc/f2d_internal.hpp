@@ -60,14 +60,12 @@ __host__ __device__ inline int64_t frame_index(int64_t iy, int64_t ix, int64_t H
 constexpr int32_t kFlip = 1;       // use F[K-1-u][K-1-v] (image adjoint)
 constexpr int32_t kZeroBorder = 2; // out-of-range source pixels read as 0
 constexpr int32_t kSumSq = 4;      // u8 path: extra output o0^2 + o1^2
-constexpr int32_t kDstVec = 8;     // every output row is 16-byte aligned (vector stores)
-constexpr int32_t kSrcVec = 16;    // every source row is 4-byte aligned (u8 word loads)
 
 // Every launcher returns hipSuccess or the launch error.
 hipError_t launch_stencil_f32(const StencilParams& p, int K, int nout, bool adjoint, int variant,
                               hipStream_t stream);
-hipError_t launch_stencil_u8(const StencilParams& p, int K, int m, bool sumsq, bool vec,
-                             int variant, hipStream_t stream);
+hipError_t launch_stencil_u8(const StencilParams& p, int K, int m, bool sumsq, int variant,
+                             hipStream_t stream);
 
 // Tile geometry of a variant, used by the host for grid sizing.
 struct TileShape {

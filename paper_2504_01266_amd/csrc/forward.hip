@@ -48,12 +48,6 @@ f2d_status size_grid(StencilParams& p, int64_t n, TileShape ts) {
   return F2D_OK;
 }
 
-bool all_aligned(const f2d_tensor* outs, int32_t n, size_t bytes) {
-  for (int32_t j = 0; j < n; ++j)
-    if (!row_aligned(outs[j], bytes)) return false;
-  return true;
-}
-
 constexpr int kMaxTemplK = 9;    // templated f32 kernels exist for K <= 9
 constexpr int kMaxTaps = 100;    // NOUT*K*K limit of the templated kernels
 
@@ -65,9 +59,8 @@ f2d_status forward_f32_zero(const Problem& pr, const f2d_tensor* outs, hipStream
   const int variant = pr.k <= kMaxTemplK ? 1 : -1;
   const TileShape tg = f32_tile(variant);
   const int64_t C = pr.image.c;
-  const int32_t vecflag = all_aligned(outs, pr.mode == F2D_CH_DEPTHWISE ? pr.m : 1, 16) ? kDstVec : 0;
   auto go = [&](StencilParams& p) -> f2d_status {
-    p.flags = kZeroBorder | vecflag;
+    p.flags = kZeroBorder;
     if (f2d_status e = size_grid(p, pr.image.n, tg)) return e;
     return hip_status(launch_stencil_f32(p, pr.k, 1, false, variant, s), "forward f32 zero-border launch");
   };
@@ -141,7 +134,6 @@ f2d_status forward_f32(const Problem& pr, const f2d_tensor* outs, int32_t n_outs
   const int variant =
       templ ? resolve_variant(kPathF32, F2D_F32, K, pr.mode, pr.image.w, pr.opts.variant) : -1;
   const TileShape ts = f32_tile(variant);
-  const int32_t vecflag = all_aligned(outs, n_outs, 16) ? kDstVec : 0;
   const int64_t C = pr.image.c;
 
   if (pr.mode == F2D_CH_SHARED) {
@@ -151,7 +143,6 @@ f2d_status forward_f32(const Problem& pr, const f2d_tensor* outs, int32_t n_outs
     p.nsrc = 1;
     p.sc_g = 1;
     p.dc_g = 1;
-    p.flags = vecflag;
     if (f2d_status e = size_grid(p, pr.image.n, ts)) return e;
     return hip_status(launch_stencil_f32(p, K, 1, false, variant, s), "forward f32 launch");
   }
@@ -168,7 +159,6 @@ f2d_status forward_f32(const Problem& pr, const f2d_tensor* outs, int32_t n_outs
       p.dc_g = 1;
       p.fg = m;
       p.fj = 1;
-      p.flags = vecflag;
       const TileShape t1 = f32_tile(1);
       if (f2d_status e = size_grid(p, pr.image.n, t1)) return e;
       return hip_status(launch_stencil_f32(p, K, m, false, 1, s), "forward f32 launch");
@@ -182,7 +172,6 @@ f2d_status forward_f32(const Problem& pr, const f2d_tensor* outs, int32_t n_outs
       p.dc_g = 1;
       p.f0 = j;
       p.fg = m;
-      p.flags = vecflag;
       if (f2d_status e = size_grid(p, pr.image.n, ts)) return e;
       hipError_t err = launch_stencil_f32(p, K, 1, false, variant, s);
       if (err != hipSuccess) return hip_status(err, "forward f32 launch");
@@ -206,7 +195,6 @@ f2d_status forward_f32(const Problem& pr, const f2d_tensor* outs, int32_t n_outs
   p.fg = nout * static_cast<int32_t>(C);
   p.fj = static_cast<int32_t>(C);
   p.fs = 1;
-  p.flags = vecflag;
   const int v = nout == 1 ? variant : 1;
   if (f2d_status e = size_grid(p, pr.image.n, f32_tile(v))) return e;
   return hip_status(launch_stencil_f32(p, K, nout, false, v, s), "forward f32 bank launch");
@@ -218,9 +206,6 @@ f2d_status forward_u8(const Problem& pr, const f2d_tensor* outs, int32_t n_outs,
   const int variant =
       templ ? resolve_variant(kPathU8, F2D_U8, K, pr.mode, pr.image.w, pr.opts.variant) : -1;
   const TileShape ts = u8_tile(variant);
-  int32_t flags = 0;
-  if (all_aligned(outs, n_outs, 16)) flags |= kDstVec;
-  if (row_aligned(pr.image, 4)) flags |= kSrcVec;
   const int64_t C = pr.image.c;
   const bool sumsq = pr.opts.epilogue == F2D_EPI_SUMSQ_PAIRS;
   const int m = pr.m;
@@ -235,9 +220,9 @@ f2d_status forward_u8(const Problem& pr, const f2d_tensor* outs, int32_t n_outs,
     p.dc_g = 1;
     p.fg = pr.mode == F2D_CH_SHARED ? 0 : m;
     p.fj = 1;
-    p.flags = flags | (sumsq ? kSumSq : 0);
+    p.flags = sumsq ? kSumSq : 0;
     if (f2d_status e = size_grid(p, pr.image.n, ts)) return e;
-    return hip_status(launch_stencil_u8(p, K, m, sumsq, true, variant, s), "forward u8 launch");
+    return hip_status(launch_stencil_u8(p, K, m, sumsq, variant, s), "forward u8 launch");
   }
   for (int j = 0; j < m; ++j) {
     StencilParams p = base_params(pr);
@@ -248,9 +233,8 @@ f2d_status forward_u8(const Problem& pr, const f2d_tensor* outs, int32_t n_outs,
     p.dc_g = 1;
     p.f0 = j;
     p.fg = m;
-    p.flags = flags;
     if (f2d_status e = size_grid(p, pr.image.n, ts)) return e;
-    hipError_t err = launch_stencil_u8(p, K, 1, false, true, variant, s);
+    hipError_t err = launch_stencil_u8(p, K, 1, false, variant, s);
     if (err != hipSuccess) return hip_status(err, "forward u8 launch");
   }
   return ok();

@@ -240,8 +240,8 @@ __global__ __launch_bounds__(kThreads) void k_grad_filter_f32(GradFilterParams p
       const int64_t y = oy0 + ty * kGfPY + jy;
       const int64_t x = ox0 + tx * kGfPX;
       const float* row = gp + (y < p.H ? y : 0) * gsh;
-      if ((p.flags & kDstVec) && y < p.H && x + kGfPX <= p.W) {
-        const float4 q = *reinterpret_cast<const float4*>(row + x);
+      if (y < p.H && x + kGfPX <= p.W) {
+        const f32x4_a4 q = *reinterpret_cast<const f32x4_a4*>(row + x);
         gv[jy][0] = q.x;
         gv[jy][1] = q.y;
         gv[jy][2] = q.z;
@@ -336,8 +336,8 @@ __global__ __launch_bounds__(kThreads) void k_grad_filter_bank_f32(GradFilterPar
         const int64_t y = oy0 + ty * kGfPY + jy;
         const int64_t x = ox0 + tx * kGfPX;
         const float* row = gp[j] + (y < p.H ? y : 0) * gsh;
-        if ((p.flags & kDstVec) && y < p.H && x + kGfPX <= p.W) {
-          const float4 q = *reinterpret_cast<const float4*>(row + x);
+        if (y < p.H && x + kGfPX <= p.W) {
+          const f32x4_a4 q = *reinterpret_cast<const f32x4_a4*>(row + x);
           gv[j][jy][0] = q.x;
           gv[j][jy][1] = q.y;
           gv[j][jy][2] = q.z;

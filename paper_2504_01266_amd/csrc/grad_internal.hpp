@@ -38,7 +38,6 @@ struct GradFilterParams {
   int64_t nf, nrep, chunks, n_units;
   int32_t mode, m, C;  // C = image channels (input channels of a bank)
   int32_t tiles_x, tiles_y, tiles_per_unit;
-  int32_t flags;  // kDstVec: G-bar rows 16-byte aligned
 };
 
 // The r-wide frame of the image adjoint, folded onto the edge pixels of out.

@@ -45,6 +45,39 @@ constexpr int kOutI32 = 0;
 constexpr int kOutF32 = 1;
 constexpr int kOutU8 = 2;
 
+typedef uint32_t u32_a1 __attribute__((aligned(1)));
+typedef uint32_t u32x2_a1 __attribute__((ext_vector_type(2), aligned(1)));
+typedef uint32_t u32x4_a1 __attribute__((ext_vector_type(4), aligned(1)));
+
+// N words from / to any byte address
+template <int N>
+__device__ __forceinline__ void load_words(const uint8_t* a, uint32_t (&w)[N]) {
+  constexpr int N4 = N / 4 * 4, N2 = N4 + (N - N4) / 2 * 2;
+#pragma unroll
+  for (int i = 0; i < N4; i += 4) {
+    const u32x4_a1 t = *reinterpret_cast<const u32x4_a1*>(a + 4 * i);
+    w[i] = t[0];
+    w[i + 1] = t[1];
+    w[i + 2] = t[2];
+    w[i + 3] = t[3];
+  }
+  if constexpr (N2 > N4) {
+    const u32x2_a1 t = *reinterpret_cast<const u32x2_a1*>(a + 4 * N4);
+    w[N4] = t[0];
+    w[N4 + 1] = t[1];
+  }
+  if constexpr (N > N2) w[N2] = *reinterpret_cast<const u32_a1*>(a + 4 * N2);
+}
+template <int N>
+__device__ __forceinline__ void store_words(uint8_t* a, const uint32_t (&w)[N]) {
+  constexpr int N4 = N / 4 * 4, N2 = N4 + (N - N4) / 2 * 2;
+#pragma unroll
+  for (int i = 0; i < N4; i += 4)
+    *reinterpret_cast<u32x4_a1*>(a + 4 * i) = u32x4_a1{w[i], w[i + 1], w[i + 2], w[i + 3]};
+  if constexpr (N2 > N4) *reinterpret_cast<u32x2_a1*>(a + 4 * N4) = u32x2_a1{w[N4], w[N4 + 1]};
+  if constexpr (N > N2) *reinterpret_cast<u32_a1*>(a + 4 * N2) = w[N2];
+}
+
 constexpr int kGThreads = 256;
 // A lane produces E = 8 or 16 consecutive output elements per row (16 for
 // 8-bit outputs of an image upsampled by 8 or more: one 16-byte store per
@@ -74,7 +107,6 @@ struct GatherParams {
   int32_t lds_rows;  // staged source rows per tile (at most); one more zero row follows
   int32_t tiles_x, tiles_y;
   int64_t n_blocks;
-  int32_t vec;  // output rows aligned for the lanes' vector stores
 };
 
 // x / s for 0 <= x < 2^32 with the launch's invariant-divisor constants
@@ -307,11 +339,8 @@ __global__ __launch_bounds__(kGThreads) void k_u8_gather(GatherParams p) {
     if (ebase < L) {
       if constexpr (OUT == kOutU8) {
         uint8_t* dp = static_cast<uint8_t*>(p.dst) + n * p.d_sn + c * p.d_sc + y * p.d_sh + ebase;
-        if (p.vec && ebase + kGElems <= L) {
-          if constexpr (E == 16)
-            *reinterpret_cast<uint4*>(dp) = make_uint4(outw[0], outw[1], outw[2], outw[3]);
-          else
-            *reinterpret_cast<uint2*>(dp) = make_uint2(outw[0], outw[1]);
+        if (ebase + kGElems <= L) {
+          store_words<E / 4>(dp, outw);
         } else {
 #pragma unroll
           for (int j = 0; j < kGElems; ++j)
@@ -319,11 +348,8 @@ __global__ __launch_bounds__(kGThreads) void k_u8_gather(GatherParams p) {
         }
       } else {
         uint32_t* dp = static_cast<uint32_t*>(p.dst) + n * p.d_sn + c * p.d_sc + y * p.d_sh + ebase;
-        if (p.vec && ebase + kGElems <= L) {
-#pragma unroll
-          for (int w4 = 0; w4 < E / 4; ++w4)
-            reinterpret_cast<uint4*>(dp)[w4] =
-                make_uint4(outw[4 * w4], outw[4 * w4 + 1], outw[4 * w4 + 2], outw[4 * w4 + 3]);
+        if (ebase + kGElems <= L) {
+          store_words<kGElems>(reinterpret_cast<uint8_t*>(dp), outw);
         } else {
 #pragma unroll
           for (int j = 0; j < kGElems; ++j)
@@ -367,39 +393,6 @@ struct DirectParams {
   int32_t strips, runs;
   int64_t n_waves;
 };
-
-typedef uint32_t u32_a1 __attribute__((aligned(1)));
-typedef uint32_t u32x2_a1 __attribute__((ext_vector_type(2), aligned(1)));
-typedef uint32_t u32x4_a1 __attribute__((ext_vector_type(4), aligned(1)));
-
-// N words from / to any byte address
-template <int N>
-__device__ __forceinline__ void load_words(const uint8_t* a, uint32_t (&w)[N]) {
-  constexpr int N4 = N / 4 * 4, N2 = N4 + (N - N4) / 2 * 2;
-#pragma unroll
-  for (int i = 0; i < N4; i += 4) {
-    const u32x4_a1 t = *reinterpret_cast<const u32x4_a1*>(a + 4 * i);
-    w[i] = t[0];
-    w[i + 1] = t[1];
-    w[i + 2] = t[2];
-    w[i + 3] = t[3];
-  }
-  if constexpr (N2 > N4) {
-    const u32x2_a1 t = *reinterpret_cast<const u32x2_a1*>(a + 4 * N4);
-    w[N4] = t[0];
-    w[N4 + 1] = t[1];
-  }
-  if constexpr (N > N2) w[N2] = *reinterpret_cast<const u32_a1*>(a + 4 * N2);
-}
-template <int N>
-__device__ __forceinline__ void store_words(uint8_t* a, const uint32_t (&w)[N]) {
-  constexpr int N4 = N / 4 * 4, N2 = N4 + (N - N4) / 2 * 2;
-#pragma unroll
-  for (int i = 0; i < N4; i += 4)
-    *reinterpret_cast<u32x4_a1*>(a + 4 * i) = u32x4_a1{w[i], w[i + 1], w[i + 2], w[i + 3]};
-  if constexpr (N2 > N4) *reinterpret_cast<u32x2_a1*>(a + 4 * N4) = u32x2_a1{w[N4], w[N4 + 1]};
-  if constexpr (N > N2) *reinterpret_cast<u32_a1*>(a + 4 * N2) = w[N2];
-}
 
 // Source offset (-1, 0, 1) that tap t (0..2) of upsampled phase ph meets.
 template <int S>
@@ -713,8 +706,6 @@ struct MixParams {
   int64_t W, row0, rows;  // output rows [row0, row0 + rows) of the buffer
   int32_t tiles_x;        // 1024-pixel segments per row
   int64_t n_blocks;
-  int32_t in_vec;   // source rows word-aligned (planar) / interleaved rows word-aligned
-  int32_t out_vec;  // output planes rows aligned for 4-pixel stores (planar output)
 };
 
 constexpr int kMixThreads = 256;
@@ -736,10 +727,9 @@ __global__ __launch_bounds__(kMixThreads) void k_u8_mix(MixParams p) {
   // x[i][k]: channel i of pixel x0 + k
   uint32_t x[CIN][kMixPx];
   if (p.s_sw == CIN && p.s_sc == 1 && CIN > 1) {  // interleaved
-    if (p.in_vec && full) {
+    if (full) {
       uint32_t wd[CIN * kMixPx / 4];
-#pragma unroll
-      for (int q = 0; q < CIN * kMixPx / 4; ++q) wd[q] = reinterpret_cast<const uint32_t*>(rp + x0 * CIN)[q];
+      load_words<CIN * kMixPx / 4>(rp + x0 * CIN, wd);
 #pragma unroll
       for (int k = 0; k < kMixPx; ++k)
 #pragma unroll
@@ -757,10 +747,9 @@ __global__ __launch_bounds__(kMixThreads) void k_u8_mix(MixParams p) {
 #pragma unroll
     for (int i = 0; i < CIN; ++i) {
       const uint8_t* cp = rp + i * p.s_sc;
-      if (p.in_vec && full) {
+      if (full) {
         uint32_t wd[kMixPx / 4];
-#pragma unroll
-        for (int q = 0; q < kMixPx / 4; ++q) wd[q] = reinterpret_cast<const uint32_t*>(cp + x0)[q];
+        load_words<kMixPx / 4>(cp + x0, wd);
 #pragma unroll
         for (int k = 0; k < kMixPx; ++k) x[i][k] = (wd[k >> 2] >> (8 * (k & 3))) & 0xffu;
       } else {
@@ -801,11 +790,12 @@ __global__ __launch_bounds__(kMixThreads) void k_u8_mix(MixParams p) {
         }
       }
       uint8_t* dp = static_cast<uint8_t*>(p.dst) + obase;
-      if (p.out_vec && full && p.d_sw == 1) {
+      if (full && p.d_sw == 1) {
+        uint32_t ow[kMixPx / 4];
 #pragma unroll
         for (int q = 0; q < kMixPx / 4; ++q)
-          reinterpret_cast<uint32_t*>(dp + x0)[q] =
-              q8[4 * q] | (q8[4 * q + 1] << 8) | (q8[4 * q + 2] << 16) | (q8[4 * q + 3] << 24);
+          ow[q] = q8[4 * q] | (q8[4 * q + 1] << 8) | (q8[4 * q + 2] << 16) | (q8[4 * q + 3] << 24);
+        store_words<kMixPx / 4>(dp + x0, ow);
       } else {
 #pragma unroll
         for (int k = 0; k < kMixPx; ++k)
@@ -813,12 +803,11 @@ __global__ __launch_bounds__(kMixThreads) void k_u8_mix(MixParams p) {
       }
     } else {
       uint32_t* dp = static_cast<uint32_t*>(p.dst) + obase;
-      if (p.out_vec && full && p.d_sw == 1) {
+      if (full && p.d_sw == 1) {
+        uint32_t ow[kMixPx];
 #pragma unroll
-        for (int q = 0; q < kMixPx / 4; ++q)
-          reinterpret_cast<uint4*>(dp + x0)[q] =
-              make_uint4(__builtin_bit_cast(uint32_t, acc[4 * q]), __builtin_bit_cast(uint32_t, acc[4 * q + 1]),
-                         __builtin_bit_cast(uint32_t, acc[4 * q + 2]), __builtin_bit_cast(uint32_t, acc[4 * q + 3]));
+        for (int k = 0; k < kMixPx; ++k) ow[k] = __builtin_bit_cast(uint32_t, acc[k]);
+        store_words<kMixPx>(reinterpret_cast<uint8_t*>(dp + x0), ow);
       } else {
 #pragma unroll
         for (int k = 0; k < kMixPx; ++k)
@@ -834,17 +823,6 @@ int64_t eff_sw(const f2d_tensor& t) { return t.stride_w <= 0 ? 1 : t.stride_w; }
 
 // Interleaved: channels adjacent (stride_c 1) and pixels C apart, C > 1.
 bool interleaved(const f2d_tensor& t) { return t.c > 1 && t.stride_c == 1 && eff_sw(t) == t.c; }
-
-// Row starts aligned to `bytes` (base pointer, row and image strides); the
-// channel stride is ignored for interleaved tensors, whose channels sit
-// inside the pixel.
-bool rows_aligned(const f2d_tensor& t, size_t bytes) {
-  if (!interleaved(t)) return row_aligned(t, bytes);
-  const size_t es = t.dtype == F2D_U8 ? 1 : 4;
-  const uintptr_t a = reinterpret_cast<uintptr_t>(t.data);
-  return a % bytes == 0 && (t.h <= 1 || (t.stride_h * es) % bytes == 0) &&
-         (t.n <= 1 || (t.stride_n * es) % bytes == 0);
-}
 
 template <int K, int P, bool TF, int OUT, int E>
 hipError_t launch_gather_one(const GatherParams& g, hipStream_t s) {
@@ -1003,7 +981,6 @@ f2d_status gather_forward(const Problem& pr, const f2d_tensor& out, int32_t scal
   g.tiles_y = static_cast<int32_t>((g.out_rows + g.th - 1) / g.th);
   g.n_blocks = im.n * g.planes_c * static_cast<int64_t>(g.tiles_x) * g.tiles_y;
   if (g.n_blocks > kMaxBlocks) return fail(F2D_EUNSUPPORTED, "u8 filter: too many tiles for one launch");
-  g.vec = rows_aligned(out, ok_out == kOutU8 ? static_cast<size_t>(elems) : 16) ? 1 : 0;
   if (g.n_blocks == 0) return ok();
   hipError_t err;
   switch (pr.k) {
@@ -1035,8 +1012,7 @@ f2d_status mix_forward(const Problem& pr, const f2d_tensor& out, hipStream_t s) 
   if (im.c > 4 || pr.c_out > 4) return fail(F2D_EUNSUPPORTED, "u8 channel mixing: at most 4 input and 4 output channels");
   const bool il = interleaved(im);
   if (!il && eff_sw(im) != 1) return fail(F2D_EUNSUPPORTED, "u8 images: planar or interleaved layouts");
-  const bool oil = interleaved(out);
-  if (!oil && eff_sw(out) != 1) return fail(F2D_EUNSUPPORTED, "u8 channel mixing: planar or interleaved outputs");
+  if (!interleaved(out) && eff_sw(out) != 1) return fail(F2D_EUNSUPPORTED, "u8 channel mixing: planar or interleaved outputs");
   const bool tf = pr.filter.dtype == F2D_F32;
   const int ok_out = out_kind(out.dtype);
   if ((tf && ok_out == kOutI32) || (!tf && ok_out == kOutF32))
@@ -1061,8 +1037,6 @@ f2d_status mix_forward(const Problem& pr, const f2d_tensor& out, hipStream_t s) 
   m.tiles_x = static_cast<int32_t>((im.w + kMixThreads * kMixPx - 1) / (kMixThreads * kMixPx));
   m.n_blocks = im.n * m.rows * m.tiles_x;
   if (m.n_blocks > kMaxBlocks) return fail(F2D_EUNSUPPORTED, "u8 channel mixing: too many tiles for one launch");
-  m.in_vec = rows_aligned(im, 4) ? 1 : 0;
-  m.out_vec = !oil && row_aligned(out, ok_out == kOutU8 ? 4 : 16) ? 1 : 0;
   if (m.n_blocks == 0) return ok();
   hipError_t e;
   switch (im.c) {

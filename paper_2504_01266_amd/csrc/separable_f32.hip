@@ -38,7 +38,6 @@ struct SepParams {
   int64_t C;
   int32_t tiles_x, tiles_y;
   int64_t n_blocks;  // N * C * tiles_y * tiles_x
-  int32_t vec;       // every output row 16-byte aligned
 };
 
 template <int K>
@@ -104,7 +103,7 @@ __global__ __launch_bounds__(kThreads) void k_separable_f32(SepParams p) {
 #pragma unroll
   for (int jy = 0; jy < 4; ++jy) {
     const int64_t oy = oy0 + ty * 4 + jy;
-    if (oy < p.rows) store_row<4>(dp + oy * p.d_sh, ox0 + tx * 4, p.W, p.vec != 0, acc[jy]);
+    if (oy < p.rows) store_row<4>(dp + oy * p.d_sh, ox0 + tx * 4, p.W, acc[jy]);
   }
 }
 
@@ -141,7 +140,6 @@ f2d_status run_forward_separable(const Problem& pr, const float* a, const float*
   p.n_blocks = im.n * im.c * static_cast<int64_t>(p.tiles_x) * p.tiles_y;
   if (p.n_blocks > kMaxBlocks)
     return fail(F2D_EUNSUPPORTED, "%lld tiles exceed one launch", static_cast<long long>(p.n_blocks));
-  p.vec = row_aligned(out, 16) ? 1 : 0;
   hipError_t e;
   switch (pr.k) {
     case 1: e = launch<1>(p, s); break;

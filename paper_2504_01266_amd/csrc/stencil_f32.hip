@@ -38,7 +38,6 @@ __device__ __forceinline__ void store_outputs(const StencilParams& p, int64_t n,
                                               int64_t oy0, int64_t ox0,
                                               const float (&acc)[NOUT][PY][PX]) {
   if constexpr (J < NOUT) {
-    const bool vec = (p.flags & kDstVec) != 0;
     const int tx = threadIdx.x % kTX;
     const int ty = threadIdx.x / kTX;
     int64_t dsh;
@@ -46,7 +45,7 @@ __device__ __forceinline__ void store_outputs(const StencilParams& p, int64_t n,
 #pragma unroll
     for (int jy = 0; jy < PY; ++jy) {
       const int64_t oy = oy0 + ty * PY + jy;
-      if (oy < p.rows) store_row<PX>(dp + oy * dsh, ox0 + tx * PX, p.W, vec, acc[J][jy]);
+      if (oy < p.rows) store_row<PX>(dp + oy * dsh, ox0 + tx * PX, p.W, acc[J][jy]);
     }
     store_outputs<NOUT, PX, PY, J + 1>(p, n, g, oy0, ox0, acc);
   }
@@ -59,7 +58,6 @@ __device__ __forceinline__ void store_outputs(const StencilParams& p, int64_t n,
 template <int PX, int PY>
 __device__ __forceinline__ void store_adjoint(const StencilParams& p, int64_t n, int64_t g, int j, int64_t oy0,
                                               int64_t ox0, const float (&acc)[PY][PX]) {
-  const bool vec = (p.flags & kDstVec) != 0;
   const int tx = threadIdx.x % kTX;
   const int ty = threadIdx.x / kTX;
   int64_t dsh;
@@ -74,7 +72,7 @@ __device__ __forceinline__ void store_adjoint(const StencilParams& p, int64_t n,
     const int64_t iy = p.row0 + oy;
     const int64_t ix0 = ox0 + tx * PX;
     if (iy >= 0 && iy < p.H && ix0 >= 0 && ix0 + PX <= p.W) {
-      store_row<PX>(dp + iy * dsh, ix0, p.W, vec, acc[jy]);
+      store_row<PX>(dp + iy * dsh, ix0, p.W, acc[jy]);
     } else {
 #pragma unroll
       for (int px = 0; px < PX; ++px) {

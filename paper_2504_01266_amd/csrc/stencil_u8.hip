@@ -4,7 +4,7 @@
 // 1 byte in), so the kernel is shaped around an uninterrupted store stream.
 // A work-group (4 waves) owns a 256-pixel-wide, 4*RS-row tile of one
 // channel.  It first stages the tile's source rows, halo included, in LDS
-// with aligned word loads (clamped byte loads only at the image edges).  Each
+// with word loads (clamped byte loads only at the image edges).  Each
 // wave then walks down its RS-row strip: every lane keeps the last K source
 // rows of its (4+K-1)-byte window in registers, reading one new row from LDS
 // per output row, and writes four consecutive pixels of every output plane
@@ -32,6 +32,8 @@ constexpr int kPitchWords = kTW / 4 + 2;  // staged source columns x0-4 .. x0+TW
 constexpr int kMaxR = 4;                  // K <= 9
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v4i_a4 __attribute__((ext_vector_type(4), aligned(4)));  // rows need not be 16-byte aligned
+typedef uint32_t u32_a1 __attribute__((aligned(1)));                 // nor source rows word-aligned
 
 template <bool SMALL>
 __device__ __forceinline__ uint32_t mul(uint32_t a, uint32_t b) {
@@ -39,18 +41,18 @@ __device__ __forceinline__ uint32_t mul(uint32_t a, uint32_t b) {
   return a * b;
 }
 
-__device__ __forceinline__ void store4(int32_t* __restrict__ dp, int64_t x0, int64_t W, bool vec,
+__device__ __forceinline__ void store4(int32_t* __restrict__ dp, int64_t x0, int64_t W,
                                        const uint32_t (&v)[4], bool nt) {
-  if (vec && x0 + 4 <= W) {
+  if (x0 + 4 <= W) {
     v4i q;
     q.x = static_cast<int>(v[0]);
     q.y = static_cast<int>(v[1]);
     q.z = static_cast<int>(v[2]);
     q.w = static_cast<int>(v[3]);
     if (nt)
-      __builtin_nontemporal_store(q, reinterpret_cast<v4i*>(dp + x0));
+      __builtin_nontemporal_store(q, reinterpret_cast<v4i_a4*>(dp + x0));
     else
-      *reinterpret_cast<v4i*>(dp + x0) = q;
+      *reinterpret_cast<v4i_a4*>(dp + x0) = q;
   } else {
 #pragma unroll
     for (int px = 0; px < 4; ++px)
@@ -63,17 +65,16 @@ __device__ __forceinline__ void store4(int32_t* __restrict__ dp, int64_t x0, int
 // columns x0-4+4d .. x0-1+4d.
 template <int LH>
 __device__ __forceinline__ void stage(uint32_t* __restrict__ lds, const uint8_t* __restrict__ sp,
-                                      int64_t sh, int64_t H, int64_t W, int64_t row_base, int64_t x0,
-                                      bool word_ok) {
+                                      int64_t sh, int64_t H, int64_t W, int64_t row_base, int64_t x0) {
   // Waves take rows (uniform row address), lanes take words.  Interior tiles
-  // (a uniform test) load aligned words; tiles touching the left or right
-  // edge, or unaligned rows, assemble each word from clamped byte loads.  All
+  // (a uniform test) load words at any alignment; tiles touching the left or
+  // right edge assemble each word from clamped byte loads.  All
   // loads of a wave are issued before the first LDS write.
   constexpr int CPL = (kPitchWords + kLanes - 1) / kLanes;
   constexpr int RPW = (LH + kWaves - 1) / kWaves;
   const int lane = threadIdx.x % kLanes;
   const int wave = threadIdx.x / kLanes;
-  const bool interior = word_ok && x0 - 4 >= 0 && x0 + 4 * kPitchWords - 4 <= W;
+  const bool interior = x0 - 4 >= 0 && x0 + 4 * kPitchWords - 4 <= W;
   uint32_t buf[RPW][CPL];
   const uint8_t* rows[RPW];
 #pragma unroll
@@ -89,7 +90,7 @@ __device__ __forceinline__ void stage(uint32_t* __restrict__ lds, const uint8_t*
 #pragma unroll
       for (int j = 0; j < CPL; ++j) {
         const int d = lane + kLanes * j < kPitchWords ? lane + kLanes * j : kPitchWords - 1;
-        buf[i][j] = *reinterpret_cast<const uint32_t*>(rows[i] + x0 - 4 + 4 * d);
+        buf[i][j] = *reinterpret_cast<const u32_a1*>(rows[i] + x0 - 4 + 4 * d);
       }
   } else {
 #pragma unroll
@@ -137,7 +138,7 @@ template <int K, int M, bool SUMSQ, int RS, bool NT, bool SMALL>
 __device__ __forceinline__ void strip(const uint32_t* __restrict__ lds, int lane, int wave,
                                       int32_t* const (&dp)[M + 1], const int64_t (&dsh)[M + 1],
                                       const uint32_t (&tap)[M][K * K], int64_t xl, int64_t W,
-                                      int64_t oy0, int nrows, bool vec) {
+                                      int64_t oy0, int nrows) {
   constexpr int WIN = 4 + K - 1;
   uint32_t win[K][WIN];
   const uint32_t* base = lds + wave * RS * kPitchWords;
@@ -164,13 +165,13 @@ __device__ __forceinline__ void strip(const uint32_t* __restrict__ lds, int lane
     }
     const int64_t oy = oy0 + i;
 #pragma unroll
-    for (int j = 0; j < M; ++j) store4(dp[j] + oy * dsh[j], xl, W, vec, o[j], NT);
+    for (int j = 0; j < M; ++j) store4(dp[j] + oy * dsh[j], xl, W, o[j], NT);
     if constexpr (SUMSQ) {
       uint32_t m2[4];
 #pragma unroll
       for (int px = 0; px < 4; ++px)
         m2[px] = mul<SMALL>(o[0][px], o[0][px]) + mul<SMALL>(o[1][px], o[1][px]);
-      store4(dp[M] + oy * dsh[M], xl, W, vec, m2, NT);
+      store4(dp[M] + oy * dsh[M], xl, W, m2, NT);
     }
   }
 }
@@ -197,7 +198,7 @@ __global__ __launch_bounds__(kThreads) void k_stencil_u8(StencilParams p) {
   const int64_t ty0 = tile_y * TH;  // first output row of the tile (band-relative)
 
   const uint8_t* sp = static_cast<const uint8_t*>(p.src[0]) + n * p.src_sn[0] + g * p.src_sc[0];
-  stage<LH>(lds, sp, p.src_sh[0], p.H, p.W, p.row0 + ty0 - R, x0, (p.flags & kSrcVec) != 0);
+  stage<LH>(lds, sp, p.src_sh[0], p.H, p.W, p.row0 + ty0 - R, x0);
 
   int32_t* dp[M + 1];
   int64_t dsh[M + 1];
@@ -232,11 +233,10 @@ __global__ __launch_bounds__(kThreads) void k_stencil_u8(StencilParams p) {
   const int64_t oy0 = ty0 + wave * RS;
   if (xl >= p.W || oy0 >= p.rows) return;  // no barriers follow
   const int nrows = static_cast<int>(p.rows - oy0 < RS ? p.rows - oy0 : RS);
-  const bool vec = (p.flags & kDstVec) != 0;
   if (small)
-    strip<K, M, SUMSQ, RS, NT, true>(lds, lane, wave, dp, dsh, tap, xl, p.W, oy0, nrows, vec);
+    strip<K, M, SUMSQ, RS, NT, true>(lds, lane, wave, dp, dsh, tap, xl, p.W, oy0, nrows);
   else
-    strip<K, M, SUMSQ, RS, NT, false>(lds, lane, wave, dp, dsh, tap, xl, p.W, oy0, nrows, vec);
+    strip<K, M, SUMSQ, RS, NT, false>(lds, lane, wave, dp, dsh, tap, xl, p.W, oy0, nrows);
 }
 
 // Runtime-K fallback: one output value per thread per filter, source read
@@ -329,9 +329,8 @@ int u8_variant_count() { return 7; }
 
 // m is 1 or 2 for the templated kernels (K <= 9); variant < 0 selects
 // the generic kernel, which handles m <= 2 for any odd K <= 31.
-hipError_t launch_stencil_u8(const StencilParams& p, int K, int m, bool sumsq, bool vec,
-                             int variant, hipStream_t stream) {
-  (void)vec;
+hipError_t launch_stencil_u8(const StencilParams& p, int K, int m, bool sumsq, int variant,
+                             hipStream_t stream) {
   if (p.n_blocks <= 0) return hipSuccess;
   if (variant < 0) {
     hipLaunchKernelGGL(k_stencil_u8_generic, dim3(static_cast<uint32_t>(p.n_blocks)),

@@ -1,0 +1,112 @@
+"""Images and outputs that start at any element and have any row pitch.
+
+The kernels move 16 bytes a lane whatever the alignment of a row, so each path
+is run on views into wider buffers (rows that start 1 to 3 elements past a
+16-byte line, odd pitches) and compared with the oracle; the bytes around the
+output view must stay as they were.  Integer operands: bit-exact.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2504_01266_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+OFFSETS = [(0, 1), (1, 0), (2, 2), (3, 4)]  # first column, extra columns after the row
+WIDTHS = [3, 4, 61, 257, 1030]
+H = 19
+
+
+def wide(r, lead, w, ofs, lo=-4, hi=5, dtype=np.float32):
+    return r.integers(lo, hi, (*lead, H, w + sum(ofs))).astype(dtype)
+
+
+def cut(t, w, ofs):
+    return t[..., ofs[0]:ofs[0] + w]
+
+
+def outbuf(lead, w, ofs, dtype):
+    return torch.full((*lead, H, w + sum(ofs)), 77, dtype=dtype, device="cuda")
+
+
+def check(buf, w, ofs, want):
+    got = buf.cpu().numpy()
+    np.testing.assert_array_equal(cut(got, w, ofs), want)
+    np.testing.assert_array_equal(got[..., :ofs[0]], np.full_like(got[..., :ofs[0]], 77))
+    np.testing.assert_array_equal(got[..., ofs[0] + w:], np.full_like(got[..., ofs[0] + w:], 77))
+
+
+@pytest.mark.parametrize("ofs", OFFSETS)
+@pytest.mark.parametrize("w", WIDTHS)
+@pytest.mark.parametrize("k", [3, 9])
+def test_f32_rows(gpu_lib, w, ofs, k):
+    r = wl.rng(71, w, k, *ofs)
+    x, f = wide(r, (2, 2), w, ofs), r.integers(-3, 4, (k, k)).astype(np.float32)
+    xd, fd = torch.from_numpy(x).cuda(), torch.from_numpy(f).cuda()
+    print(w, ofs, k, flush=True)
+    xc = np.ascontiguousarray(cut(x, w, ofs))
+    for border in ("clamp", "zero"):
+        want = np.asarray(oracle.forward(xc, f, "shared", border=border), np.float32)
+        for v in (0, 2, 3, 4) if border == "clamp" else (0,):
+            y = outbuf((2, 2), w, ofs, torch.float32)
+            gpu_lib.forward(cut(xd, w, ofs), fd, outs=[cut(y, w, ofs)], variant=v, border=border)
+            check(y, w, ofs, want)
+        if border == "clamp":
+            for v in range(1, 9):
+                y = outbuf((2, 2), w, ofs, torch.float32)
+                gpu_lib.RaggedBatch([cut(xd[i], w, ofs) for i in (0, 1)], [cut(y[i], w, ofs) for i in (0, 1)],
+                                    [fd, fd], variant=v).run()
+                check(y, w, ofs, want)
+    a, b = f[0].copy(), f[1].copy()
+    y = outbuf((2, 2), w, ofs, torch.float32)
+    gpu_lib.forward_separable(cut(xd, w, ofs), torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda(),
+                              out=cut(y, w, ofs))
+    check(y, w, ofs, np.asarray(oracle.forward(xc, np.outer(a, b), "shared"), np.float32))
+    g = wide(r, (2, 2), w, ofs)
+    gi = outbuf((2, 2), w, ofs, torch.float32)
+    _, gf = gpu_lib.backward(cut(xd, w, ofs), fd, cut(torch.from_numpy(g).cuda(), w, ofs),
+                             grad_input=cut(gi, w, ofs))
+    gc = np.ascontiguousarray(cut(g, w, ofs))
+    check(gi, w, ofs, oracle.grad_input(gc, f, (2, 2, H, w), "shared"))
+    np.testing.assert_array_equal(gf.cpu().numpy(), oracle.grad_filter(xc, gc, (1, 1, k, k), "shared")[0, 0])
+
+
+@pytest.mark.parametrize("ofs", OFFSETS)
+@pytest.mark.parametrize("w", WIDTHS)
+def test_u8_rows(gpu_lib, w, ofs):
+    r = wl.rng(73, w, *ofs)
+    x = wide(r, (2, 3), w, ofs, 0, 256, np.uint8)
+    xd = torch.from_numpy(x).cuda()
+    xc = np.ascontiguousarray(cut(x, w, ofs))
+    print(w, ofs, flush=True)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    # single-channel integer stencils (planar, int32 out)
+    for k in (3, 7):
+        f = r.integers(-3, 4, (k, k)).astype(np.int32)
+        y = outbuf((2, 3), w, ofs, torch.int32)
+        gpu_lib.forward(cut(xd, w, ofs), dev(f), outs=[cut(y, w, ofs)])
+        check(y, w, ofs, oracle.forward_int(xc, f, "shared"))
+    # 5x5 into bytes and floats
+    f = r.integers(-3, 4, (5, 5)).astype(np.float32)
+    full = np.asarray(oracle.forward(xc.astype(np.float32), f, "shared"))
+    y = outbuf((2, 3), w, ofs, torch.float32)
+    gpu_lib.forward(cut(xd, w, ofs), dev(f), outs=[cut(y, w, ofs)])
+    check(y, w, ofs, full.astype(np.float32))
+    y = outbuf((2, 3), w, ofs, torch.uint8)
+    gpu_lib.forward(cut(xd, w, ofs), dev(f), outs=[cut(y, w, ofs)])
+    check(y, w, ofs, np.clip(full, 0, 255).astype(np.uint8))
+    # channel mixing, planar and interleaved sources
+    m = r.integers(-2, 3, (2, 3, 1, 1)).astype(np.int32)
+    want = np.einsum("oc,nchw->nohw", m[:, :, 0, 0], xc.astype(np.int32))
+    il = cut(xd, w, ofs)
+    if w > 3:
+        il = torch.empty(2, H, w + sum(ofs), 3, dtype=torch.uint8, device="cuda").permute(0, 3, 1, 2)
+        il.copy_(xd)
+        il = cut(il, w, ofs)
+    for src in (cut(xd, w, ofs), il):
+        for dt in (torch.int32, torch.uint8):
+            y = outbuf((2, 2), w, ofs, dt)
+            gpu_lib.forward(src, dev(m), mode="bank", outs=[cut(y, w, ofs)])
+            check(y, w, ofs, want if dt == torch.int32 else np.clip(want, 0, 255).astype(np.uint8))
