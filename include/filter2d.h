@@ -291,7 +291,7 @@ int64_t filter2d_batched_plan(const f2d_batch_item* items, int32_t n_items, int3
  * filter2d_batched -- one launch over every tile of every item.  Variants
  * 1..4: one work-group per tile, each finding its item in the prefix table;
  * variants 5..8 (the same four tilings): one work-group per run of 4
- * consecutive tiles, staged in 16-byte chunks.  Items must have h and w
+ * consecutive tiles.  Items must have h and w
  * below 2^31 (the plan returns F2D_EUNSUPPORTED otherwise).
  * items_dev and tile_prefix_dev (n_items + 2 words) are device copies of the
  * plan's inputs and outputs.  The call reads nothing from them on the host,

@@ -65,11 +65,11 @@ int variant_count(int path) {
   }
 }
 
-int resolve_variant(int path, int dtype, int k, int channels, int64_t w, int requested) {
+int resolve_variant(int path, int dtype, int k, int channels, int64_t w, int requested, int dflt) {
   if (requested > 0) return requested;
   std::lock_guard<std::mutex> lk(g_tune_mu);
   auto it = g_tune.find(TuneKey(path, dtype, k, channels, width_class(w)));
-  return it == g_tune.end() ? 1 : it->second;
+  return it == g_tune.end() ? dflt : it->second;
 }
 
 void record_variant(int path, int dtype, int k, int channels, int64_t w, int variant) {

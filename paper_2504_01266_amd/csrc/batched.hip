@@ -3,16 +3,18 @@
 // The host plan turns the items (images of different sizes, each with its own
 // K x K filter) into a prefix sum of per-item tile counts, followed by a tag
 // that records the tiling variant and K it was planned for.  The kernel runs
-// one work-group per tile of the global tile list (the hardware starts the
-// next work-group as soon as one retires); a work-group finds the owning item
-// by a 64-way search of the prefix table and runs the same tile code as the
-// single-image FP32 path (SHARED mode, clamp-to-edge).  A table planned for
+// one work-group per tile (or short run of tiles) of the global tile list (the
+// hardware starts the next work-group as soon as one retires); a work-group
+// finds the owning item by a 64-way search of the prefix table and filters
+// the tile as the single-image FP32 path does (SHARED mode, clamp-to-edge; the
+// same order of every sum).  A table planned for
 // another variant or K is recognised on the device from its tag and the
 // launch then writes nothing.  The grid comes from the plan's tile count and
 // nothing is read on the host at launch time, so the call can be captured in
 // a hipGraph and replayed.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstring>
 #include <vector>
@@ -64,68 +66,18 @@ __device__ __forceinline__ int find_item(const int64_t* __restrict__ prefix, int
   return lo;
 }
 
-template <int K, int PX, int PY>
-__global__ __launch_bounds__(kThreads) void k_batched_f32(const f2d_batch_item* __restrict__ items,
-                                                          const int64_t* __restrict__ prefix,
-                                                          int32_t n_items, int64_t total_tiles,
-                                                          int64_t tag) {
-  using G = Geom<K, PX, PY>;
-  // a table planned for another tile shape or K: write nothing (uniform)
-  if (prefix[n_items + 1] != tag) return;
-  __shared__ float4 lds4[(G::LDS_WORDS + 3) / 4];
-  float* lds = reinterpret_cast<float*>(lds4);
-  const int tx = threadIdx.x % kTX;
-  const int ty = threadIdx.x / kTX;
-
-  // One tile per work-group in practice (the grid covers 2^30 tiles); each
-  // round of the loop maps its work-groups onto a contiguous run of tiles
-  // per XCD, so neighbouring tiles share halo rows in one L2.
-  const int64_t grid = gridDim.x;
-  for (int64_t t0 = 0; t0 < total_tiles; t0 += grid) {
-    const int64_t nb = total_tiles - t0 < grid ? total_tiles - t0 : grid;
-    if (blockIdx.x >= nb) break;  // uniform
-    const int64_t t = t0 + xcd_remap(blockIdx.x, nb);
-    const int lo = find_item(prefix, n_items, t);
-    const f2d_batch_item& it = items[lo];
-    const uint32_t tiles_x = static_cast<uint32_t>((it.w + G::TW - 1) / G::TW);
-    const uint32_t per_plane = tiles_x * static_cast<uint32_t>((it.h + G::TH - 1) / G::TH);
-    const uint32_t local = static_cast<uint32_t>(t - prefix[lo]);  // one item has < 2^32 tiles
-    const uint32_t c = local / per_plane;
-    if (c >= it.c) continue;  // uniform; unreachable with a matching plan
-    const uint32_t r = local - c * per_plane;
-    const uint32_t tile_y = r / tiles_x;
-    const uint32_t tile_x = r - tile_y * tiles_x;
-    const int64_t oy0 = static_cast<int64_t>(tile_y) * G::TH, ox0 = static_cast<int64_t>(tile_x) * G::TW;
-
-    float tap[1][K * K];
-    const auto* fc = const_ptr(it.filter);
-#pragma unroll
-    for (int e = 0; e < K * K; ++e) tap[0][e] = fc[e];
-    const auto sp = global_ptr(static_cast<const float*>(it.image)) + c * it.in_stride_c;
-    stage_tile<K, PX, PY, false>(lds, sp, it.in_stride_h, it.h, it.w, oy0, ox0);
-    float acc[1][PY][PX];
-#pragma unroll
-    for (int jy = 0; jy < PY; ++jy)
-#pragma unroll
-      for (int px = 0; px < PX; ++px) acc[0][jy][px] = 0.0f;
-    __syncthreads();
-    accumulate<K, 1, PX, PY>(lds, tap, acc);
-
-    const auto dp = global_ptr(static_cast<float*>(it.out)) + c * it.out_stride_c;
-#pragma unroll
-    for (int jy = 0; jy < PY; ++jy) {
-      const int64_t oy = oy0 + ty * PY + jy;
-      if (oy < it.h) store_row<PX>(dp + oy * it.out_stride_h, ox0 + tx * PX, it.w, acc[0][jy]);
-    }
-    __syncthreads();  // the next tile overwrites the LDS tile
-  }
-}
-
-// ------------------------------------------------------------ tile runs --
 // Variants 5..8 (the tilings of 1..4): each work-group takes a short run of
 // consecutive tiles of the global tile list (usually neighbours in one image,
 // so their halos are L2 hits), finds the first tile's item once and steps to
-// the next tiles without divisions.
+// the next tiles without divisions.  Variants 1..4 are runs of one tile.
+//
+// Bound by HBM at 3x3 and 5x5, by the VALU at 7x7 and 9x9.  Variants 1..4
+// were a kernel of their own that staged with 4-byte loads; runs of one tile
+// of this kernel took 64 images of 256 to 4096 rows and columns from 1267 to
+// 1167 us at 3x3, 1541 to 1336 at 5x5, 2216 to 1755 at 7x7 and 3615 to 2453
+// at 9x9, where runs of 4 tiles take 2243: there the 81 taps' move into vector
+// registers is paid once per run.  At 3x3 to 7x7 runs of 4 take 1609, 1598
+// and 1778 (a tile's loads start only when the tile before it is finished).
 //
 // Staging moves 16-byte chunks: the LDS tile starts 4 columns left of the
 // output tile (so every LDS row is 16-byte aligned and the chunk grid is the
@@ -307,12 +259,13 @@ __device__ __forceinline__ void accumulate_off(const float* __restrict__ lds, co
 }
 
 template <int K, int PX, int PY>
-__global__ __launch_bounds__(kThreads) void k_batched_pipe(const f2d_batch_item* __restrict__ items,
-                                                           const int64_t* __restrict__ prefix,
-                                                           int32_t n_items, int64_t total_tiles,
-                                                           int64_t tag, int32_t per_group) {
+__global__ __launch_bounds__(kThreads) void k_batched_f32(const f2d_batch_item* __restrict__ items,
+                                                          const int64_t* __restrict__ prefix,
+                                                          int32_t n_items, int64_t total_tiles,
+                                                          int64_t tag, int64_t per_group) {
   using G = PGeom<K, PX, PY>;
-  if (prefix[n_items + 1] != tag) return;  // uniform, see k_batched_f32
+  // a table planned for another tile shape or K: write nothing (uniform)
+  if (prefix[n_items + 1] != tag) return;
   __shared__ f32x4_t lds4[G::LDS_WORDS / 4];
   float* lds = reinterpret_cast<float*>(lds4);
   const int tx = threadIdx.x % kTX;
@@ -380,32 +333,18 @@ struct Shape {
   static constexpr int TH = kTY * PY, TW = kTX * PX;
 };
 
-// One work-group per tile (capped at 2^30, the loop takes any remainder): the
-// hardware starts a new work-group as soon as one retires, so one tile's
-// staging overlaps other tiles' arithmetic.
+// The hardware hands runs to work-groups as they retire (no tail of idle CUs
+// behind a static split).  A list of more than 2^30 runs gets longer ones.
+constexpr int64_t kTilesPerGroup = 4;  // variants 5..8
+
 template <int K, int PX, int PY>
 hipError_t launch(const f2d_batch_item* items, const int64_t* prefix, int32_t n, int64_t total, int64_t tag,
-                  hipStream_t s) {
+                  bool runs, hipStream_t s) {
   constexpr int64_t kMaxGrid = int64_t{1} << 30;
-  const int64_t g = total < kMaxGrid ? total : kMaxGrid;
+  const int64_t per_group = std::max(runs ? kTilesPerGroup : 1, (total + kMaxGrid - 1) / kMaxGrid);
+  const int64_t g = (total + per_group - 1) / per_group;
   hipLaunchKernelGGL((k_batched_f32<K, PX, PY>), dim3(static_cast<uint32_t>(g)), dim3(kThreads), 0, s,
-                     items, prefix, n, total, tag);
-  return hipGetLastError();
-}
-
-// Runs of a few tiles per work-group: the search for the first tile's item
-// and the tile decode are paid once per run, and the hardware still hands
-// runs to work-groups as they retire (no tail of idle CUs behind a static
-// split).
-constexpr int32_t kTilesPerGroup = 4;
-
-template <int K, int PX, int PY>
-hipError_t launch_pipe(const f2d_batch_item* items, const int64_t* prefix, int32_t n, int64_t total,
-                       int64_t tag, hipStream_t s) {
-  const int64_t g = (total + kTilesPerGroup - 1) / kTilesPerGroup;
-  if (g > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_batched_pipe<K, PX, PY>), dim3(static_cast<uint32_t>(g)), dim3(kThreads), 0, s,
-                     items, prefix, n, total, tag, kTilesPerGroup);
+                     items, prefix, n, total, tag, per_group);
   return hipGetLastError();
 }
 
@@ -413,15 +352,11 @@ template <int K>
 hipError_t by_variant(int variant, const f2d_batch_item* items, const int64_t* prefix, int32_t n,
                       int64_t total, hipStream_t s) {
   const int64_t tag = plan_tag(variant, K);
-  switch (variant) {
-    case 2: return launch<K, 4, 2>(items, prefix, n, total, tag, s);
-    case 3: return launch<K, 4, 8>(items, prefix, n, total, tag, s);
-    case 4: return launch<K, 8, 2>(items, prefix, n, total, tag, s);
-    case 5: return launch_pipe<K, 4, 4>(items, prefix, n, total, tag, s);
-    case 6: return launch_pipe<K, 4, 2>(items, prefix, n, total, tag, s);
-    case 7: return launch_pipe<K, 4, 8>(items, prefix, n, total, tag, s);
-    case 8: return launch_pipe<K, 8, 2>(items, prefix, n, total, tag, s);
-    default: return launch<K, 4, 4>(items, prefix, n, total, tag, s);
+  switch (variant > 4 ? variant - 4 : variant) {
+    case 2: return launch<K, 4, 2>(items, prefix, n, total, tag, variant > 4, s);
+    case 3: return launch<K, 4, 8>(items, prefix, n, total, tag, variant > 4, s);
+    case 4: return launch<K, 8, 2>(items, prefix, n, total, tag, variant > 4, s);
+    default: return launch<K, 4, 4>(items, prefix, n, total, tag, variant > 4, s);
   }
 }
 
@@ -475,7 +410,19 @@ int64_t batched_plan(const f2d_batch_item* items, int32_t n_items, int32_t dtype
         return -fail(F2D_EINVAL, "item %d: output planes overlap", i);
     }
   }
-  const int v = resolve_variant(kPathBatched, dtype, k, F2D_CH_SHARED, max_width(items, n_items), *variant);
+  // Default tiling, from the number of 64 x 64 tiles (every variant gives the same bits):
+  // - below 4 a CU, 32 x 64 tiles (variant 2): 8 images of 16 to 256 rows and
+  //   columns, 180 tiles: 5.5 against 6.1 us at 3x3, 6.1 against 7.2 at 7x7,
+  //   8.0 against 9.7 at 9x9; with 2241 tiles 16.2 against 15.8, 24.6 against
+  //   25.5, 40.2 against 33.8;
+  // - 9x9 from 16 a CU on, runs of 4 tiles (variant 5): 4785 tiles 63.3
+  //   against 64.3 us, 9207 tiles 107 against 116, 212427 tiles 2243 against
+  //   2453; with 2241 tiles 37.0 against 33.8.
+  int64_t t64 = 0;
+  for (int32_t i = 0; i < n_items; ++i)
+    t64 += items[i].c * ((items[i].h + 63) / 64) * ((items[i].w + 63) / 64);
+  const int dflt = t64 < 1024 ? 2 : (k == 9 && t64 >= 4096 ? 5 : 1);
+  const int v = resolve_variant(kPathBatched, dtype, k, F2D_CH_SHARED, max_width(items, n_items), *variant, dflt);
   const TileShape ts = batched_tile(v);
   tile_prefix[0] = 0;
   for (int32_t i = 0; i < n_items; ++i) {

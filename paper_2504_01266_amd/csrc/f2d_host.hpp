@@ -37,7 +37,7 @@ f2d_status check_common(const f2d_tensor* image, const f2d_filter* filter, const
 int64_t numel(const f2d_tensor& t);
 
 // tuning table (api.hip)
-int resolve_variant(int path, int dtype, int k, int channels, int64_t w, int requested);
+int resolve_variant(int path, int dtype, int k, int channels, int64_t w, int requested, int dflt = 1);
 void record_variant(int path, int dtype, int k, int channels, int64_t w, int variant);
 int variant_count(int path);
 
