@@ -93,7 +93,7 @@ size_t backward_workspace(const Problem& pr) {
   if (pr.image.dtype == F2D_BF16) return bank_backward_bf16_workspace(pr);
   if (pr.image.dtype != F2D_F32) return 0;
   const FilterPlan fp = filter_plan(pr);
-  const bool mfma = bank_f32_wgrad_mfma(pr.mode, pr.k, pr.c_out, pr.image.c, pr.image.w);
+  const bool mfma = bank_f32_wgrad_mfma(pr.mode, pr.k, pr.c_out, pr.image.c, pr.image.n, pr.image.h, pr.image.w);
   return frame_bytes(pr) + partial_bytes(mfma ? bank_plan(pr).sets * fp.nf : fp.n_units, pr.k);
 }
 
@@ -293,7 +293,7 @@ f2d_status run_backward(const Problem& pr, const f2d_tensor* grad_outs, int32_t 
   if (grad_filter) {
     const FilterPlan fp = filter_plan(pr);
     float* partial = reinterpret_cast<float*>(static_cast<char*>(ws) + frame_bytes(pr));
-    if (!empty && bank_f32_wgrad_mfma(pr.mode, K, pr.c_out, im.c, im.w)) {
+    if (!empty && bank_f32_wgrad_mfma(pr.mode, K, pr.c_out, im.c, im.n, im.h, im.w)) {
       const f2d_tensor& g = grad_outs[0];
       BankF32WgradParams q;
       std::memset(&q, 0, sizeof(q));

@@ -317,7 +317,13 @@ struct WgradF32Geom {
   static constexpr int NX = QC + K - 1;  // X columns of a lane and row
   static constexpr int GP = SW + 4;      // LDS row pitches (floats, 16-byte aligned rows)
   static constexpr int XP = (SW + K - 1 + 7) / 4 * 4;
-  static constexpr int FLUSH = 4;        // rows between two flushes of the accumulators
+  // Error, not speed, sets these: with chains of 64 steps and one sum over a
+  // unit the weights were further from the 64-bit ones than the VALU kernel's
+  // (16 -> 64, 3x3, 2 x 44 x 40: 1.6e-7 against 1.1e-7, now 0.95e-7; 64 -> 64,
+  // 1x1, 8 x 1000^2: 4.1e-7 against 3.1e-7, now 2.4e-7).  3x3 on 4 x 16 x
+  // 1024^2 -> 64: 763 us then, 785 now (VALU 1950).
+  static constexpr int FLUSH = K == 1 ? 4 : 8;  // MFMA steps (4 pixels each) of an accumulation chain
+  static constexpr int SEG = K == 1 ? 32 : 64;  // rows of a wave before its sums go to memory
 };
 
 template <int K>
@@ -386,9 +392,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                           ? xs0 + static_cast<int64_t>(p.run_strips) * G::SW : p.W;
   const float* gn = p.g + n * p.g_sn;
   const float* xn = p.x + n * p.x_sn;
-  const int rs = (p.run_rows + splits - 1) / splits;  // rows of a split
   const int64_t ye = ys + p.run_rows < p.H ? ys + p.run_rows : p.H;
-  const int64_t y0 = ys + sp * rs, y1 = y0 + rs < ye ? y0 + rs : ye;  // this wave's rows
+  // of the current segment: first row, rows of a split, this wave's rows
+  int64_t yseg, y0, y1;
+  int rs;
 
   // staging: thread = (plane tid / 16 of a slot, 16-byte chunk tid % 16)
   const int gslots = p.obw * splits, xslots = p.ibw * splits;
@@ -435,13 +442,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (i < gslots) {
-        const int64_t y = row(ys + (i / p.obw) * rs + it);
+        const int64_t y = row(yseg + (i / p.obw) * rs + it);
         gv[i] = *reinterpret_cast<const f32x4_u*>(gn + plane_g(i, pln) * p.g_sc + y * p.g_sh + gl);
       }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (i < xslots) {
-        const float* r = xn + row(ys + (i / p.ibw) * rs + it + LEAD) * p.x_sh;
+        const float* r = xn + row(yseg + (i / p.ibw) * rs + it + LEAD) * p.x_sh;
         xv[i] = *reinterpret_cast<const f32x4_u*>(r + plane_x(i, pln) * p.x_sc + xl);
         if (K > 1 && tid < 16 * NE) xe[i] = r[plane_x(i, epn) * p.x_sc + el];
       }
@@ -484,90 +491,103 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
       }
   };
 
-  f32x4 acc[NT], sum[NT];
-#pragma unroll
-  for (int e = 0; e < NT; ++e) acc[e] = sum[e] = f32x4{0.f, 0.f, 0.f, 0.f};
   float xr[NU][G::NX], g[G::QC];
   const float* gr = lds + ((sp * p.obw + bo) * 16 + l16) * G::GP + G::QC * q;
   const float* xw = lds + gslots * 16 * G::GP + ((sp * p.ibw + bi) * 16 + l16) * G::XP + G::QC * q;
+  const int c = (ib0 + bi) * 16 + l16;
+  bool first = true;
   for (int64_t xs = xs0; xs < xs1; xs += G::SW) {
     set_strip(xs);
-    {
-      // the NU - 1 X rows above the first one, straight from memory
-      const int c = (ib0 + bi) * 16 + l16;
-      const float* xp = xn + static_cast<int64_t>(c < p.CI ? c : p.CI - 1) * p.x_sc;
+    for (yseg = ys; yseg < ye; yseg += splits * G::SEG) {
+      const int64_t yend = yseg + splits * G::SEG < ye ? yseg + splits * G::SEG : ye;
+      rs = static_cast<int>((yend - yseg + splits - 1) / splits);
+      y0 = yseg + sp * rs;
+      y1 = y0 + rs < yend ? y0 + rs : yend;
+      f32x4 sum[NT];
 #pragma unroll
-      for (int u = 0; u + 1 < NU; ++u)
-        wgrad_row_x<K>(xp + row(y0 - G::R + U0 + u) * p.x_sh, x0 + G::QC * q, p.W, xin, xr[u]);
-    }
-    issue(0);
-    store(lds);
-    __syncthreads();
-    for (int it = 0; it < rs; ++it) {
-      if (it + 1 < rs) issue(it + 1);
-      const int off = (it & 1) * bufw;
+      for (int e = 0; e < NT; ++e) sum[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+      {
+        // the NU - 1 X rows above the first one, straight from memory
+        const float* xp = xn + static_cast<int64_t>(c < p.CI ? c : p.CI - 1) * p.x_sc;
 #pragma unroll
-      for (int i = 0; i < G::QC / 4; ++i) {
-        const f32x4 t = *reinterpret_cast<const f32x4*>(gr + off + 4 * i);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) g[4 * i + e] = t[e];
+        for (int u = 0; u + 1 < NU; ++u)
+          wgrad_row_x<K>(xp + row(y0 - G::R + U0 + u) * p.x_sh, x0 + G::QC * q, p.W, xin, xr[u]);
       }
+      issue(0);
+      store(lds);
+      __syncthreads();
+      for (int it = 0; it < rs; ++it) {
+        if (it + 1 < rs) issue(it + 1);
+        const int off = (it & 1) * bufw;
 #pragma unroll
-      for (int i = 0; i < (G::NX + 3) / 4; ++i) {
-        const f32x4 t = *reinterpret_cast<const f32x4*>(xw + off + 4 * i);
+        for (int i = 0; i < G::QC / 4; ++i) {
+          const f32x4 t = *reinterpret_cast<const f32x4*>(gr + off + 4 * i);
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (4 * i + e < G::NX) xr[NU - 1][4 * i + e] = t[e];
+          for (int e = 0; e < 4; ++e) g[4 * i + e] = t[e];
+        }
+#pragma unroll
+        for (int i = 0; i < (G::NX + 3) / 4; ++i) {
+          const f32x4 t = *reinterpret_cast<const f32x4*>(xw + off + 4 * i);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (4 * i + e < G::NX) xr[NU - 1][4 * i + e] = t[e];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // short chains (the first MFMA of each starts from zero): see FLUSH
+        if (y0 + it < y1) {
+#pragma unroll
+          for (int h = 0; h < G::QC; h += G::FLUSH) {
+            f32x4 acc[NT];
+#pragma unroll
+            for (int j = h; j < h + G::FLUSH; ++j)
+#pragma unroll
+              for (int u = 0; u < NU; ++u)
+#pragma unroll
+                for (int v = 0; v < K; ++v)
+                  acc[u * K + v] = mfma4(g[j], xr[u][j + v], j == h ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[u * K + v]);
+#pragma unroll
+            for (int e = 0; e < NT; ++e) sum[e] += acc[e];
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u + 1 < NU; ++u)
+#pragma unroll
+          for (int i = 0; i < G::NX; ++i) xr[u][i] = xr[u + 1][i];
+        if (it + 1 < rs) store(lds + ((it + 1) & 1) * bufw);
+        __syncthreads();
       }
-      __builtin_amdgcn_sched_barrier(0);
-      if (y0 + it < y1) {
+      // the row splits are added in order
+      for (int s = 1; s < splits; ++s) {
+        if (sp == s) {
 #pragma unroll
-        for (int j = 0; j < G::QC; ++j)
+          for (int e = 0; e < NT; ++e) shm[(bw * NT + e) * 64 + lane] = sum[e];
+        }
+        __syncthreads();
+        if (sp == 0) {
 #pragma unroll
-          for (int u = 0; u < NU; ++u)
-#pragma unroll
-            for (int v = 0; v < K; ++v) acc[u * K + v] = mfma4(g[j], xr[u][j + v], acc[u * K + v]);
+          for (int e = 0; e < NT; ++e) sum[e] += shm[(bw * NT + e) * 64 + lane];
+        }
+        __syncthreads();
       }
-      __builtin_amdgcn_sched_barrier(0);
-      // short chains: every 256 pixels go to a second accumulator
-      if (it % G::FLUSH == G::FLUSH - 1 || it + 1 == rs) {
+      // the unit's sums so far are in its partial (this lane's own entries)
+      if (sp == 0 && c < p.CI) {
 #pragma unroll
-        for (int e = 0; e < NT; ++e) {
-          sum[e] += acc[e];
-          acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < 4; ++j) {
+          const int oo = (ob0 + bo) * 16 + 4 * q + j;
+          if (oo >= p.CO) break;
+          const int64_t f = static_cast<int64_t>(oo) * p.CI + c;
+          float* dst = p.partial + (unit * p.CO * p.CI + f) * KK + U0 * K;
+          if (!first) {
+#pragma unroll
+            for (int e = 0; e < NT; ++e) sum[e][j] += dst[e];
+          }
+#pragma unroll
+          for (int e = 0; e < NT; ++e) dst[e] = sum[e][j];
         }
       }
-#pragma unroll
-      for (int u = 0; u + 1 < NU; ++u)
-#pragma unroll
-        for (int i = 0; i < G::NX; ++i) xr[u][i] = xr[u + 1][i];
-      if (it + 1 < rs) store(lds + ((it + 1) & 1) * bufw);
-      __syncthreads();
+      first = false;
     }
-  }
-  // the row splits are added in order
-  for (int s = 1; s < splits; ++s) {
-    if (sp == s) {
-#pragma unroll
-      for (int e = 0; e < NT; ++e) shm[(bw * NT + e) * 64 + lane] = sum[e];
-    }
-    __syncthreads();
-    if (sp == 0) {
-#pragma unroll
-      for (int e = 0; e < NT; ++e) sum[e] += shm[(bw * NT + e) * 64 + lane];
-    }
-    __syncthreads();
-  }
-  const int c = (ib0 + bi) * 16 + l16;
-  if (sp != 0 || c >= p.CI) return;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int oo = (ob0 + bo) * 16 + 4 * q + j;
-    if (oo >= p.CO) break;
-    const int64_t f = static_cast<int64_t>(oo) * p.CI + c;
-    float* dst = p.partial + (unit * p.CO * p.CI + f) * KK + U0 * K;
-#pragma unroll
-    for (int e = 0; e < NT; ++e) dst[e] = sum[e][j];
   }
 }
 
@@ -689,10 +709,13 @@ bool bank_f32_conv_mfma(int mode, int K, int64_t src, int64_t out, int64_t w) {
 // grad_filter pads both channel counts to sixteens.  Measured as above: 1x1
 // 3 x 16 1.6, 8 x 8 1.1, 1 x 64 0.8; 3x3 8 x 16 1.24, 8 x 8 0.83, 16 x 64
 // 2.8; 5x5 8 x 16 0.8, 16 x 16 1.2, 16 x 64 1.9.
-bool bank_f32_wgrad_mfma(int mode, int K, int64_t co, int64_t ci, int64_t w) {
+// Small 1x1 layers stay on the VALU, whose fewer partial sets are added sooner
+// (multiply-adds 0.4M 15.8 / 20.3 us, 0.9M 16.0 / 18.9, 13M 32.6 / 33.5, 18M
+// 27.0 / 25.2, 28M 36.0 / 25.5); 3x3 with 32M: 32.8 / 27.7.
+bool bank_f32_wgrad_mfma(int mode, int K, int64_t co, int64_t ci, int64_t n, int64_t h, int64_t w) {
   if (mode != F2D_CH_BANK || w < 4 || ci > 65536 || co > 65536) return false;
   const int64_t pairs = ci * co, padded = (ci + 15) / 16 * 16 * ((co + 15) / 16 * 16);
-  if (K == 1) return 16 * pairs >= 3 * padded;
+  if (K == 1) return 16 * pairs >= 3 * padded && static_cast<double>(pairs) * n * h * w >= 16e6;
   if (K == 3) return 2 * pairs >= padded;
   if (K == 5) return 4 * pairs >= 3 * padded;
   return false;

@@ -52,7 +52,7 @@ struct BankF32WgradParams {
 // Whether a map from src to out channels, or a grad_filter, of this shape
 // takes these kernels (else the VALU ones).
 bool bank_f32_conv_mfma(int mode, int K, int64_t src, int64_t out, int64_t w);
-bool bank_f32_wgrad_mfma(int mode, int K, int64_t co, int64_t ci, int64_t w);
+bool bank_f32_wgrad_mfma(int mode, int K, int64_t co, int64_t ci, int64_t n, int64_t h, int64_t w);
 void bank_f32_wgrad_plan(int64_t n, int64_t h, int64_t w, int64_t co, int64_t ci, int64_t max_sets,
                          BankF32WgradPlan* plan);
 hipError_t launch_bank_f32_conv(const BankF32Params& p, int K, bool adjoint, hipStream_t s);

@@ -89,3 +89,16 @@ def test_gradients_repeat_bitwise(gpu_lib):
     a = gpu_lib.backward(x, f, g, mode="bank")
     b = gpu_lib.backward(x, f, g, mode="bank")
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("case", [(32, 64, 256, 70, 4, 1), (32, 64, 256, 66, 5, 3), (512, 16, 16, 258, 4, 3)])
+def test_weight_gradient_over_several_row_segments(gpu_lib, case):
+    """Units with more rows than a wave adds up before its sums go to memory
+    (with one and with four row splits), so the partials are added to."""
+    n, ci, co, h, w, k = case
+    x, g = ints(12, n, ci, h, w), ints(13, n, co, h, w)
+    f = ints(14, co, ci, k, k)
+    print(case, flush=True)
+    _, gf = gpu_lib.backward(dev(x), dev(f), dev(g), mode="bank", need_input=False)
+    assert np.array_equal(gf.double().cpu().numpy(),
+                          oracle.grad_filter(x.astype(np.float64), g.astype(np.float64), f.shape, "bank"))
