@@ -240,8 +240,11 @@ f2d_status run_backward(const Problem& pr, const f2d_tensor* grad_outs, int32_t 
     e.planes = im.n * im.c;
 
     const bool templ = K <= 9;
-    const TileShape ts = f32_tile(templ ? 1 : -1);
     const int64_t r = (K - 1) / 2;
+    // (launches that sum over several source planes keep the 64 x 64 tiles)
+    const int variant = !templ ? -1 : (pr.mode == F2D_CH_BANK || p.st_s != 0
+                                           ? 1 : f32_default_variant(K, im.n * im.c, im.h + 2 * r, im.w + 2 * r));
+    const TileShape ts = f32_tile(variant);
     if (templ) {
       // zero-border flipped correlation over the image and its r-wide frame
       p.row0 = -r;
@@ -267,7 +270,7 @@ f2d_status run_backward(const Problem& pr, const f2d_tensor* grad_outs, int32_t 
     p.n_blocks = im.n * p.groups * static_cast<int64_t>(p.tiles_x) * p.tiles_y;
     if (p.n_blocks > kMaxBlocks) return fail(F2D_EUNSUPPORTED, "image too large for one launch");
     if (!templ) p.flags |= kFlip | kZeroBorder;
-    hipError_t err = launch_stencil_f32(p, K, nout, true, templ ? 1 : -1, s);
+    hipError_t err = launch_stencil_f32(p, K, nout, true, variant, s);
     if (err != hipSuccess) return hip_status(err, "grad_input launch");
     if (templ) {
       FoldParams fo;

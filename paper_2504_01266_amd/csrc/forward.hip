@@ -51,14 +51,21 @@ f2d_status size_grid(StencilParams& p, int64_t n, TileShape ts) {
 constexpr int kMaxTemplK = 9;    // templated f32 kernels exist for K <= 9
 constexpr int kMaxTaps = 100;    // NOUT*K*K limit of the templated kernels
 
+// Default tiling of the launches that write one plane from one plane (BANK
+// sums over source planes keep the 64 x 64 tiles).
+int plain_variant(const Problem& pr) {
+  if (pr.mode == F2D_CH_BANK) return 1;
+  return f32_default_variant(pr.k, pr.image.n * pr.image.c, pr.rows, pr.image.w);
+}
+
 // Zero borders (out-of-image neighbours add nothing, as in the paper's
 // sharpen): one output plane per work-group tile with zero-border staging,
-// the 64 x 64 templated kernel for K <= 9 and the runtime-K kernel above
-// (DEPTHWISE: one launch per filter index).
+// the templated kernel for K <= 9 and the runtime-K kernel above (DEPTHWISE:
+// one launch per filter index).
 f2d_status forward_f32_zero(const Problem& pr, const f2d_tensor* outs, hipStream_t s) {
-  const int variant = pr.k <= kMaxTemplK ? 1 : -1;
-  const TileShape tg = f32_tile(variant);
   const int64_t C = pr.image.c;
+  const int variant = pr.k <= kMaxTemplK ? plain_variant(pr) : -1;
+  const TileShape tg = f32_tile(variant);
   auto go = [&](StencilParams& p) -> f2d_status {
     p.flags = kZeroBorder;
     if (f2d_status e = size_grid(p, pr.image.n, tg)) return e;
@@ -132,7 +139,7 @@ f2d_status forward_f32(const Problem& pr, const f2d_tensor* outs, int32_t n_outs
   const int K = pr.k;
   const bool templ = K <= kMaxTemplK;
   const int variant =
-      templ ? resolve_variant(kPathF32, F2D_F32, K, pr.mode, pr.image.w, pr.opts.variant) : -1;
+      templ ? resolve_variant(kPathF32, F2D_F32, K, pr.mode, pr.image.w, pr.opts.variant, plain_variant(pr)) : -1;
   const TileShape ts = f32_tile(variant);
   const int64_t C = pr.image.c;
 

@@ -224,20 +224,30 @@ hipError_t go(const StencilParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// zero-border forward: one output plane per tile, 64 x 64 tiles
-template <int K>
+// zero-border forward: one output plane per tile (variants 1, 2 and 4)
+template <int K, int PX, int PY>
 hipError_t go_zero(const StencilParams& p, hipStream_t stream) {
-  hipLaunchKernelGGL((k_stencil_f32<K, 1, false, false, 4, 4, true>), dim3(static_cast<uint32_t>(p.n_blocks)),
+  hipLaunchKernelGGL((k_stencil_f32<K, 1, false, false, PX, PY, true>), dim3(static_cast<uint32_t>(p.n_blocks)),
                      dim3(kThreads), 0, stream, p);
   return hipGetLastError();
+}
+template <int K>
+hipError_t zero_by_variant(const StencilParams& p, int variant, hipStream_t stream) {
+  switch (variant) {
+    case 2: return go_zero<K, 4, 2>(p, stream);
+    case 4: return go_zero<K, 8, 2>(p, stream);
+    default: return go_zero<K, 4, 4>(p, stream);
+  }
 }
 
 template <int K, int NOUT, bool ADJ>
 hipError_t by_variant(const StencilParams& p, int variant, hipStream_t stream) {
-  if constexpr (NOUT == 1 && !ADJ) {
+  if constexpr (NOUT == 1) {
     switch (variant) {
       case 2: return go<K, NOUT, ADJ, 4, 2>(p, stream);
-      case 3: return go<K, NOUT, ADJ, 4, 8>(p, stream);
+      case 3:
+        if constexpr (!ADJ) return go<K, NOUT, ADJ, 4, 8>(p, stream);
+        return hipErrorInvalidValue;
       case 4: return go<K, NOUT, ADJ, 8, 2>(p, stream);
       default: return go<K, NOUT, ADJ, 4, 4>(p, stream);
     }
@@ -255,7 +265,7 @@ hipError_t by_nout(const StencilParams& p, int nout, bool adj, int variant, hipS
       if constexpr (4 * K * K <= kMaxTaps) return by_variant<K, 4, true>(p, 1, stream);
       return hipErrorInvalidValue;
     }
-    return by_variant<K, 1, true>(p, 1, stream);
+    return by_variant<K, 1, true>(p, variant, stream);
   }
   switch (nout) {
     case 2:
@@ -282,6 +292,27 @@ TileShape f32_tile(int variant) {
 
 int f32_variant_count() { return 4; }
 
+// The default tiling of a single-output launch (every variant gives the same
+// bits), from its number of 64 x 64 tiles.  Variant 1 / the choice, in us:
+// - up to two a CU, 32 x 64 tiles (variant 2), more and shorter work-groups:
+//   3 x 240 x 320 3x3 6.7 / 5.9, 9x9 8.4 / 6.7; 1080 x 1920 (510 tiles) 3x3
+//   7.5 / 7.3, 9x9 11.3 / 10.8; at 720 tiles 8.6 / 9.4 and 14.1 / 14.0.
+// - beyond, where the VALU and not memory is the bound, 32 x 128 tiles (variant
+//   4: 16 window values for 8 outputs, where variant 1 reads 12 for 4): 5x5
+//   and 7x7 on 3 x 1080 x 1920 14.6 / 13.7 and 18.4 / 17.5, on 5 of them (7650
+//   tiles) 49.1 / 46.4 and 65.0 / 59.3; from 12240 tiles on 7x7 is slower (111
+//   / 117); 9x9 gains at every size (3 x 4320 x 7680 275 / 269, 16 x 3 x
+//   2048^2 571 / 533).  3x3 loses 5 to 8 percent.
+// Zero borders and the adjoint as the clamped forward: adjoint 3 x 64 x 64 9x9
+//   17.2 / 14.9, 3 x 2160 x 3840 7x7 67.4 / 63.1, 16 x 3 x 2048^2 9x9 661 / 633.
+// Narrow images would leave most of a 128-column tile empty.
+int f32_default_variant(int K, int64_t planes, int64_t rows, int64_t w) {
+  const int64_t tiles = planes * ((rows + 63) / 64) * ((w + 63) / 64);
+  if (tiles <= 512) return 2;
+  if (w >= 512 && (K == 9 || (K >= 5 && tiles < 8192))) return 4;
+  return 1;
+}
+
 // Templated kernels exist for K <= 9 with NOUT*K*K <= 100 (taps in SGPRs);
 // everything else runs the generic kernel (the caller sizes the grid with
 // f32_tile(-1) in that case and passes nout = 1).
@@ -293,14 +324,14 @@ hipError_t launch_stencil_f32(const StencilParams& p, int K, int nout, bool adjo
                        dim3(kThreads), 0, stream, p);
     return hipGetLastError();
   }
-  if (p.flags & kZeroBorder) {  // forward with zero borders (variant 1 tiling)
+  if (p.flags & kZeroBorder) {  // forward with zero borders
     if (nout != 1 || adjoint) return hipErrorInvalidValue;
     switch (K) {
-      case 1: return go_zero<1>(p, stream);
-      case 3: return go_zero<3>(p, stream);
-      case 5: return go_zero<5>(p, stream);
-      case 7: return go_zero<7>(p, stream);
-      case 9: return go_zero<9>(p, stream);
+      case 1: return zero_by_variant<1>(p, variant, stream);
+      case 3: return zero_by_variant<3>(p, variant, stream);
+      case 5: return zero_by_variant<5>(p, variant, stream);
+      case 7: return zero_by_variant<7>(p, variant, stream);
+      case 9: return zero_by_variant<9>(p, variant, stream);
       default: return hipErrorInvalidValue;
     }
   }

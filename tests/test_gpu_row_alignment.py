@@ -110,3 +110,20 @@ def test_u8_rows(gpu_lib, w, ofs):
             y = outbuf((2, 2), w, ofs, dt)
             gpu_lib.forward(src, dev(m), mode="bank", outs=[cut(y, w, ofs)])
             check(y, w, ofs, want if dt == torch.int32 else np.clip(want, 0, 255).astype(np.uint8))
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 70, 130), (2, 30, 37, 511), (2, 30, 37, 577), (2, 37, 33, 515)])
+@pytest.mark.parametrize("k", [3, 5, 7, 9])
+def test_default_tilings(gpu_lib, shape, k):
+    """The tilings that the number of tiles, K and the width choose: forward
+    with either border, grad_input over the image and its frame."""
+    r = wl.rng(79, k, *shape)
+    x, g = (r.integers(-4, 5, shape).astype(np.float32) for _ in range(2))
+    f = r.integers(-3, 4, (k, k)).astype(np.float32)
+    xd, gd, fd = (torch.from_numpy(a).cuda() for a in (x, g, f))
+    print(shape, k, flush=True)
+    for border in ("clamp", "zero"):
+        y = gpu_lib.forward(xd, fd, border=border)
+        np.testing.assert_array_equal(y.cpu().numpy(), oracle.forward(x, f, "shared", border=border))
+    gi, _ = gpu_lib.backward(xd, fd, gd, need_filter=False)
+    np.testing.assert_array_equal(gi.cpu().numpy(), oracle.grad_input(g, f, shape, "shared"))
