@@ -552,7 +552,7 @@ def suite(torch, B, wl, reps, only=None):
             torch.cuda.empty_cache()
 
     if want('bank_f32'):
-        # the FP32 comparison path (VALU): the same 32-image bank in FP32
+        # the same 32-image bank in FP32 (matrix cores in FP32; fractions of the VALU's rate)
         for k in (3, 5):
             bt = bank_tensors(torch, wl, k, fp32=True)
             x32, g32, w32 = bt["x32"], bt["g32"], bt["w32"]
@@ -564,7 +564,7 @@ def suite(torch, B, wl, reps, only=None):
             ws = torch.empty(B.backward_workspace(x32, w32, mode="bank"), dtype=torch.uint8, device="cuda")
             ms_f = t.per_call_ms(lambda: B.forward(x32, w32, mode="bank", outs=[y]), 2, warmup=1)
             ms_b = t.per_call_ms(lambda: B.backward(x32, w32, g32, mode="bank", workspace=ws, grad_input=gi), 2, warmup=1)
-            res[f"bank_f32_k{k}"] = {"shape": f"32x16x1024x1024 f32 -> 64 ch f32, {k}x{k} (VALU path)",
+            res[f"bank_f32_k{k}"] = {"shape": f"32x16x1024x1024 f32 -> 64 ch f32, {k}x{k}",
                                      "fwd_ms": round(ms_f, 3), "bwd_ms": round(ms_b, 3),
                                      "fwd_mpix_taps_s": round(bb["taps"] / (ms_f * 1e-3) / 1e6, 1),
                                      "fwd_bwd_mpix_taps_s": round(3 * bb["taps"] / ((ms_f + ms_b) * 1e-3) / 1e6, 1),

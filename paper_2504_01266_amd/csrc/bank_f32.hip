@@ -12,7 +12,7 @@
 // Bound by the matrix cores: 154.6 TFLOP/s in a large FP32 product on this
 // card (the clock falls to 2.2 GHz under it).  16 x 16 x 1024^2 -> 64, 3 x 3:
 // forward 6.25 -> 2.88 ms (107 TFLOP/s, matrix cores busy 77% of the cycles),
-// grad_input 7.32 -> 3.1 ms, grad_filter 8.68 -> 2.86 ms against the VALU
+// grad_input 7.32 -> 3.1 ms, grad_filter 8.68 -> 2.95 ms against the VALU
 // kernels, which stay for shapes that the padding to 4 x 16 channels makes
 // slower here (bank_f32_conv_mfma, bank_f32_wgrad_mfma).
 //
