@@ -600,6 +600,16 @@ hipError_t launch_reduce_partials(float* partial, float* out, int64_t nf, int kk
   constexpr int64_t kSeg = 32;  // items per first-pass segment
   const int64_t nseg = (count + kSeg - 1) / kSeg;
   const int64_t col_blocks = (m + 255) / 256;
+  // Few partials: one launch, a work-group per output reading every set (kk or
+  // more floats apart, so beyond some 64k values the coalesced first pass pays
+  // for its launch and its 32 dependent steps).  grad_filter of 3 x 240 x 320
+  // 3x3 14.1 -> 8.9 us, 3 x 511 x 767 3x3 18.3 -> 10.6, 9x9 31.0 -> 22.9, 4 x 3 x
+  // 1024^2 3x3 (27648 values) 29.5 -> 27.3.
+  if (count > 0 && m * count <= 65536) {
+    hipLaunchKernelGGL(k_reduce_rows, dim3(static_cast<uint32_t>(m)), dim3(256), 0, s, partial, out, nf, kk,
+                       chunks, count, int64_t{1});
+    return hipGetLastError();
+  }
   if (nseg > 0) {
     hipLaunchKernelGGL(k_reduce_segments, dim3(static_cast<uint32_t>(col_blocks), static_cast<uint32_t>(nseg)),
                        dim3(256), 0, s, partial, nf, kk, chunks, count, kSeg);
