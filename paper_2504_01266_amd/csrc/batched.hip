@@ -19,6 +19,7 @@
 #include <cstring>
 #include <vector>
 
+#include "chunk_window.hpp"
 #include "f2d_host.hpp"
 #include "f2d_internal.hpp"
 #include "stencil_tile.hpp"
@@ -165,31 +166,29 @@ __device__ __forceinline__ void load_chunks(f32x4_t (&v)[N], const int32_t (&cro
                                             const Cursor& cu) {
   using G = PGeom<K, PX, PY>;
   static_assert(N == G::CPT, "one register chunk per staged chunk");
-  // extents below 2^31 (checked by the plan): 32-bit clamps
-  const int32_t H = static_cast<int32_t>(it.h), W = static_cast<int32_t>(it.w);
+  // extents below 2^31 (checked by the plan): 32-bit positions
+  const int32_t W = static_cast<int32_t>(it.w);
   const int64_t sh = it.in_stride_h;
-  const int32_t row0 = static_cast<int32_t>(cu.ty) * G::TH - G::R;
-  const int32_t col0 = static_cast<int32_t>(cu.tx) * G::TW - 4;
+  const ChunkWindow win =
+      chunk_window<G::PITCH>(static_cast<int32_t>(cu.ty) * G::TH - G::R, static_cast<int32_t>(cu.tx) * G::TW - 4,
+                             static_cast<int32_t>(it.h), W);
   const auto sp = global_ptr(static_cast<const float*>(it.image)) + cu.c * it.in_stride_c;
-  const bool inside = col0 >= 0 && col0 + G::PITCH <= W;  // uniform
   using V = const __attribute__((address_space(1))) f32x4u_t;
 #pragma unroll
   for (int i = 0; i < G::CPT; ++i) {
     if (crow[i] >= G::LH) continue;  // past the tile (last chunks only)
-    int32_t gy = row0 + crow[i];
-    gy = gy < 0 ? 0 : (gy >= H ? H - 1 : gy);
-    const auto rp = sp + static_cast<int64_t>(gy) * sh;
-    const int32_t gx = col0 + ccol[i];
-    if (inside) {
-      const f32x4u_t t = *reinterpret_cast<V*>(rp + gx);
+    const auto rp = sp + static_cast<int64_t>(win.row(crow[i])) * sh;
+    if (win.inside) {  // uniform
+      const f32x4u_t t = *reinterpret_cast<V*>(rp + (win.col0 + ccol[i]));
       v[i] = f32x4_t{t.x, t.y, t.z, t.w};
     } else if (W >= 4) {
-      const int32_t xs = gx < 0 ? 0 : (gx > W - 4 ? W - 4 : gx);
+      int32_t d = 0;
+      const int32_t xs = win.four(ccol[i], &d);
       const f32x4u_t u = *reinterpret_cast<V*>(rp + xs);
       const f32x4_t t{u.x, u.y, u.z, u.w};
-      const int d = gx - xs;  // element q is column clamp(gx + q) = xs + clamp(d + q, 0, 3)
       v[i] = f32x4_t{pick4(t, d), pick4(t, d + 1), pick4(t, d + 2), pick4(t, d + 3)};
     } else {
+      const int32_t gx = win.col0 + ccol[i];
       float e[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) e[q] = rp[gx + q < 0 ? 0 : (gx + q >= W ? W - 1 : gx + q)];
