@@ -166,7 +166,7 @@ PyObject* py_forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Py_DECREF(r);
     if (PyErr_Occurred()) return nullptr;
   }
-  THPObjectPtr list;
+  THPObjectPtr list, seq;  // seq holds given outputs (and what makes them) until the call is enqueued
   std::vector<f2d_tensor> descs;
   if (a[5] == Py_None) {
     int64_t count = 1;
@@ -190,7 +190,8 @@ PyObject* py_forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
       PyList_SET_ITEM(list.get(), j, w);
     }
   } else {
-    THPObjectPtr seq(PySequence_Fast(a[5], "outs must be a sequence of tensors"));
+    if (PyObject_Size(a[5]) < 0) return nullptr;  // TypeError: iterators without a length are refused
+    seq = PySequence_Fast(a[5], "outs must be a sequence of tensors");
     if (!seq) return nullptr;
     const Py_ssize_t count = PySequence_Fast_GET_SIZE(seq.get());
     descs.resize(count);

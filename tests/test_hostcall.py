@@ -1,6 +1,9 @@
 """The native marshalling module on calls that never reach a kernel (CPU
 tensors, refused by the library or before it): the errors are those of the
 ctypes descriptors, and refused calls return the library's status."""
+import ctypes
+import weakref
+
 import pytest
 import torch
 
@@ -66,3 +69,62 @@ def test_refused_calls_return_the_status_and_outputs(native):
     assert status != B.OK and gf is None
     with pytest.raises(ValueError):
         native.backward(IMG, TAPS, [IMG], 0, False, True, None, None, torch.zeros(8), 0)
+
+
+# ---- what the module hands to the library, seen by functions in its place --
+
+P = ctypes.POINTER
+ENTRY = {
+    "filter2d_forward": (ctypes.c_int32, P(B.F2dTensor), P(B.F2dFilter), P(B.F2dOpts), P(B.F2dTensor),
+                         ctypes.c_int32, ctypes.c_void_p),
+    "filter2d_upsample_forward": (ctypes.c_int32, P(B.F2dTensor), P(B.F2dFilter), ctypes.c_int32, P(B.F2dOpts),
+                                  P(B.F2dTensor), ctypes.c_void_p),
+    "filter2d_forward_separable": (ctypes.c_int32, P(B.F2dTensor), ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32,
+                                   P(B.F2dOpts), P(B.F2dTensor), ctypes.c_void_p),
+    "filter2d_backward_workspace": (ctypes.c_size_t, P(B.F2dTensor), P(B.F2dFilter), P(B.F2dOpts)),
+    "filter2d_backward": (ctypes.c_int32, P(B.F2dTensor), P(B.F2dFilter), P(B.F2dTensor), ctypes.c_int32,
+                          P(B.F2dOpts), P(B.F2dTensor), ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t,
+                          ctypes.c_void_p),
+}
+
+
+@pytest.fixture
+def hooked(native):
+    """Replaces C entry points by Python functions for one test."""
+    lib, kept = B.load(), []
+
+    def connect(**hooks):
+        def address(name):
+            if name not in hooks:
+                return ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+            kept.append(ctypes.CFUNCTYPE(*ENTRY[name])(hooks[name]))
+            return ctypes.cast(kept[-1], ctypes.c_void_p).value
+        native.connect(*[address(n) for n in ENTRY])
+
+    yield connect
+    connect()
+
+
+def test_outputs_without_a_length_are_refused(native):
+    for make in (lambda: (torch.empty_like(IMG) for _ in range(1)), lambda: map(torch.empty_like, [IMG])):
+        with pytest.raises(TypeError):
+            fwd(native, outs=make())
+
+
+def test_outputs_made_by_a_sequence_live_until_the_call(native, hooked):
+    class Fresh:  # sized and iterable, keeping nothing
+        refs = []
+
+        def __len__(self):
+            return 2
+
+        def __iter__(self):
+            for _ in range(2):
+                t = torch.empty(1, 3, 8, 9)
+                self.refs.append(weakref.ref(t))
+                yield t
+
+    alive = []
+    hooked(filter2d_forward=lambda *a: alive.append([r() is not None for r in Fresh.refs]) or B.OK)
+    status, outs = fwd(native, filt=torch.zeros(6, 1, 3, 3), mode=1, outs=Fresh())
+    assert status == B.OK and alive == [[True, True]] and isinstance(outs, Fresh)
