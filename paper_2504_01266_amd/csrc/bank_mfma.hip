@@ -646,7 +646,7 @@ __device__ __forceinline__ void mfma_sweep(const uint16_t* w_pass, Src&& xsrc, i
 // MFMA operands: A = 16 pixels x 32 k (the source tile), B = 32 k x 16 output
 // channels (the weights), so D[pixel 4q + j][channel l16]: each lane holds 4
 // consecutive pixels of one output channel and writes them with one store.
-template <int K, int OT, int PT, int CG, int NW, bool ADJ, typename TS, bool OUT_BF16>
+template <int K, int OT, int PT, int CG, int NW, bool ADJ, typename TS, bool OUT_BF16, bool VEC>
 __global__ __launch_bounds__(64 * NW) void k_bank_conv(BankParams p) {
   using G = ConvGeom<K, OT, PT, CG, NW>;
   constexpr int HP = G::HP;
@@ -688,9 +688,9 @@ __global__ __launch_bounds__(64 * NW) void k_bank_conv(BankParams p) {
   int og;
   decode(t, n, og, oy0, ox0);
   Raw<TS, G::NT> st;
-  stage_load<G, K, CG, ADJ, TS>(p, n, oy0, ox0, wave, lane, st);
+  stage_load<G, K, CG, ADJ, TS, NW, G::LH, VEC>(p, n, oy0, ox0, wave, lane, st);
   load_weights<G, K, OT, CG, ADJ>(p, og, tid, wl);
-  stage_store<G, K, CG, ADJ, TS>(p, oy0, ox0, wave, lane, st, sl0);
+  stage_store<G, K, CG, ADJ, TS, NW, G::LH, false, VEC>(p, oy0, ox0, wave, lane, st, sl0);
   __syncthreads();
 
   int cur = 0;
@@ -702,7 +702,7 @@ __global__ __launch_bounds__(64 * NW) void k_bank_conv(BankParams p) {
     int64_t n2, oy2, ox2;
     int og2;
     decode(more ? t_next : t, n2, og2, oy2, ox2);
-    stage_load<G, K, CG, ADJ, TS>(p, n2, oy2, ox2, wave, lane, st);
+    stage_load<G, K, CG, ADJ, TS, NW, G::LH, VEC>(p, n2, oy2, ox2, wave, lane, st);
     __builtin_amdgcn_sched_barrier(0);  // keep every prefetch load ahead of the MFMA loop
 
     const uint16_t* b_lane = sl0 + cur * G::S_ELEMS + b_off;
@@ -724,7 +724,7 @@ __global__ __launch_bounds__(64 * NW) void k_bank_conv(BankParams p) {
           constexpr int u0 = s - S0, u1 = s == G::STEPS - 1 ? G::NT : s - S0 + 1;
 #pragma unroll
           for (int u = u0 < 0 ? 0 : u0; u < u1; ++u)
-            stage_store_unit<G, K, CG, ADJ, TS>(p, oy2, ox2, wave, lane, st, sl_next, u);
+            stage_store_unit<G, K, CG, ADJ, TS, NW, G::LH, false, VEC>(p, oy2, ox2, wave, lane, st, sl_next, u);
         }
       });
       // acc[a][b][j] = output channel (og*NP + P)*OTP*16 + 16a + l16, pixel
@@ -738,8 +738,8 @@ __global__ __launch_bounds__(64 * NW) void k_bank_conv(BankParams p) {
       // is done reading (uniform branch)
       if (og2 != og || G::NBUF == 1) __syncthreads();
       if (og2 != og) load_weights<G, K, OT, CG, ADJ>(p, og2, tid, wl);
-      if constexpr (G::NBUF == 2) stage_fix<G, K, CG, ADJ, TS>(p, oy2, ox2, wave, lane, st, sl_next);
-      if constexpr (G::NBUF == 1) stage_store<G, K, CG, ADJ, TS>(p, oy2, ox2, wave, lane, st, sl0);
+      if constexpr (G::NBUF == 2) stage_fix<G, K, CG, ADJ, TS, NW, G::LH, false, VEC>(p, oy2, ox2, wave, lane, st, sl_next);
+      if constexpr (G::NBUF == 1) stage_store<G, K, CG, ADJ, TS, NW, G::LH, false, VEC>(p, oy2, ox2, wave, lane, st, sl0);
     }
     __syncthreads();  // tile t+1 staged; everyone done with buffer cur
     if (!more) break;
@@ -1731,7 +1731,7 @@ hipError_t conv_go(const BankParams& pin, hipStream_t s) {
       if constexpr (RING)
         kern = reinterpret_cast<const void*>(k_bank_conv_ring<K, OT, PT, CG, ADJ, TS, OB, VEC>);
       else
-        kern = reinterpret_cast<const void*>(k_bank_conv<K, OT, PT, CG, NW, ADJ, TS, OB>);
+        kern = reinterpret_cast<const void*>(k_bank_conv<K, OT, PT, CG, NW, ADJ, TS, OB, VEC>);
       e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
       if (e != hipSuccess) return e;
       int per_cu = 0, cus = 0;
@@ -1754,7 +1754,7 @@ hipError_t conv_go(const BankParams& pin, hipStream_t s) {
   else {
     const int64_t g = p.n_tiles < grid ? p.n_tiles : grid;
     if (g <= 0) return hipSuccess;
-    hipLaunchKernelGGL((k_bank_conv<K, OT, PT, CG, NW, ADJ, TS, OB>), dim3(static_cast<uint32_t>(g)),
+    hipLaunchKernelGGL((k_bank_conv<K, OT, PT, CG, NW, ADJ, TS, OB, VEC>), dim3(static_cast<uint32_t>(g)),
                        dim3(G::THREADS), lds, s, p);
     return hipGetLastError();
   }
@@ -1809,10 +1809,33 @@ hipError_t conv_wide_go(const BankParams& p, hipStream_t s) {
   return conv_go<K, 1, 4, 8, 8, ADJ, TS, OB>(p, s);
 }
 
+// Rows of fewer than 8 columns: the kernels below with element staging.  The
+// channel groups, and so the order of every sum, are those of wider rows;
+// tiles are 32 columns, and the outputs come in ones and fours (twos where
+// LDS holds no more).  3x3 into BF16, 64 images: 3 x 512 x 4 -> 16 30 us and 16 x
+// 512 x 7 -> 64 103 us (one kernel for 64 channels and 16 outputs: 144 and 633;
+// element staging as a branch of the wide kernels: 36 and 148).
+template <int K, bool ADJ, typename TS, bool OB>
+hipError_t conv_narrow(const BankParams& p, int ot, int cg, hipStream_t s) {
+  if constexpr (!ADJ) {
+    if (ot == 4 && cg == 1) return conv_go<K, 4, 2, 1, 8, ADJ, TS, OB, false>(p, s);
+    if (ot == 4 && cg == 2) return conv_go<K, 4, 2, 2, 8, ADJ, TS, OB, false>(p, s);
+    if constexpr (K < 5) {
+      if (ot == 4 && cg == 4) return conv_go<K, 4, 2, 4, 8, ADJ, TS, OB, false>(p, s);
+      if (ot == 2 && cg == 8) return conv_go<K, 2, 4, 8, 8, ADJ, TS, OB, false>(p, s);
+    }
+    if (ot == 2 && cg == 4) return conv_go<K, 2, 2, 4, 8, ADJ, TS, OB, false>(p, s);
+  }
+  if (ot != 1) return hipErrorNotSupported;
+  if (cg == 1) return conv_go<K, 1, 2, 1, 8, ADJ, TS, OB, false>(p, s);
+  if (cg == 2) return conv_go<K, 1, 2, 2, 8, ADJ, TS, OB, false>(p, s);
+  if (cg == 4) return conv_go<K, 1, 2, 4, 8, ADJ, TS, OB, false>(p, s);
+  return conv_go<K, 1, 4, 8, 8, ADJ, TS, OB, false>(p, s);
+}
+
 template <int K, bool ADJ, typename TS, bool OB>
 hipError_t conv_by_shape(const BankParams& p, int ot, int cg, hipStream_t s) {
-  // fewer than 8 columns: one shape that takes any channel counts
-  if (!p.s_vec) return conv_go<K, 1, 4, 8, 8, ADJ, TS, OB, false>(p, s);
+  if (!p.s_vec) return conv_narrow<K, ADJ, TS, OB>(p, ot, cg, s);
   // instantiated (OT, CG) pairs, eight waves; 64-pixel tile rows (PT = 4),
   // 128 for 64 outputs from 9..16 inputs, where two source tiles of that
   // width still fit beside the weights; the adjoint's outputs are the
@@ -1865,7 +1888,7 @@ bool conv_shape(int64_t ci, int64_t co, int64_t w, int k, int* ot, int* cg) {
   if (g8 > 8) return false;
   *cg = g8 <= 1 ? 1 : (g8 <= 2 ? 2 : (g8 <= 4 ? 4 : 8));
   *ot = co <= 16 ? 1 : (co <= 32 ? 2 : 4);
-  if (w < 8) *ot = 1;
+  if (w < 8 && *ot == 2) *ot = 4;  // (conv_narrow)
   // keep weights + source tile within LDS
   if (*cg == 8 && *ot == 4) *ot = 2;
   if (*cg == 8 && k == 5) *ot = 1;

@@ -469,3 +469,35 @@ def test_odd_widths_and_offsets_are_bit_exact(gpu_lib, cio, w, k):
         gi, gf = gpu_lib.backward(cut(xb), fb, cut(up), mode="bank")
         assert_same(host(gi), want_i)
         assert_same(host(gf), want_f)
+
+
+@pytest.mark.parametrize("w", [1, 4, 7])
+@pytest.mark.parametrize("cio", [(3, 16), (8, 40), (16, 64), (16, 20), (32, 24), (40, 64)])
+@pytest.mark.parametrize("k", [1, 3, 5])
+def test_narrow_rows_sum_in_the_order_of_wider_ones(gpu_lib, cio, w, k):
+    """Rows of fewer than 8 columns have staging of their own; every sum is
+    taken in the order of wider rows.  The image among 8 copies of its edge
+    columns gives the same bits in its own columns (Gaussian data, so another
+    order of the channels shows), and so does grad_input away from the edges
+    that the border folds onto."""
+    cin, cout = cio
+    h = 9
+    r = wl.rng(67, cin, cout, w, k)
+    x, _ = bf(r.standard_normal((2, cin, h, w), dtype=np.float32))
+    f, _ = bf(r.standard_normal((cout, cin, k, k), dtype=np.float32))
+    cols = torch.tensor([min(max(i, 0), w - 1) for i in range(-8, w + 8)], device="cuda")
+    print(cio, w, k, flush=True)
+    for dt in (torch.float32, torch.bfloat16):
+        got = gpu_lib.forward(x, f, mode="bank", out_dtype=dt)
+        want = gpu_lib.forward(x[..., cols].contiguous(), f, mode="bank", out_dtype=dt)
+        assert torch.equal(got, want[..., 8:8 + w])
+    if cin > 16 or cout > 32:
+        return
+    for up in (torch.float32, torch.bfloat16):
+        g = torch.from_numpy(r.standard_normal((2, cout, h, w), dtype=np.float32)).cuda().to(up)
+        gw = torch.zeros(2, cout, h, w + 16, device="cuda", dtype=up)
+        gw[..., 8:8 + w] = g
+        gi, _ = gpu_lib.backward(x, f, g, mode="bank", need_filter=False)
+        gi_w, _ = gpu_lib.backward(x[..., cols].contiguous(), f, gw, mode="bank", need_filter=False)
+        e = 1 if k > 1 else 0
+        assert torch.equal(gi[..., e:h - e, e:w - e], gi_w[..., e:h - e, 8 + e:8 + w - e])
