@@ -134,8 +134,12 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream",
                       lambda device: torch.cuda.current_stream(device).cuda_stream)
 
 
+def _stream_address():  # (native calls ask for it last, after they have checked their arguments)
+    return _raw_stream(_current_device())
+
+
 def _stream():
-    return ctypes.c_void_p(_raw_stream(_current_device()))
+    return ctypes.c_void_p(_stream_address())
 
 
 def tensor_desc(t, dtype=None):
@@ -204,8 +208,7 @@ def forward(image, filt, mode="shared", epilogue=EPI_NONE, rows=None, outs=None,
         load()
     m = _MODES[mode] if isinstance(mode, str) else int(mode)
     b = _BORDERS[border] if isinstance(border, str) else int(border)
-    status, outs = _native.forward(image, filt, m, epilogue, rows, outs, variant, out_dtype, b,
-                                   _raw_stream(_current_device()))
+    status, outs = _native.forward(image, filt, m, epilogue, rows, outs, variant, out_dtype, b, _stream_address)
     if status != OK:
         _check(status)
     return outs if m == DEPTHWISE else outs[0]
@@ -217,7 +220,7 @@ def upsample_forward(image, filt, scale, out=None, out_dtype=None, border="clamp
     if _native is None:
         load()
     b = _BORDERS[border] if isinstance(border, str) else int(border)
-    status, out = _native.upsample(image, filt, int(scale), out, out_dtype, b, _raw_stream(_current_device()))
+    status, out = _native.upsample(image, filt, int(scale), out, out_dtype, b, _stream_address)
     if status != OK:
         _check(status)
     return out
@@ -229,7 +232,7 @@ def forward_separable(image, a, b, rows=None, out=None):
     if _native is None:
         load()
     r0, r1 = (None, None) if rows is None else rows
-    status, out = _native.separable(image, a, b, r0, r1, out, _raw_stream(_current_device()))
+    status, out = _native.separable(image, a, b, r0, r1, out, _stream_address)
     if status != OK:
         _check(status)
     return out
@@ -255,7 +258,7 @@ def backward(image, filt, grad_outs, mode="shared", need_input=True, need_filter
         grad_outs = [grad_outs]
     m = _MODES[mode] if isinstance(mode, str) else int(mode)
     status, gi, gf = _native.backward(image, filt, grad_outs, m, need_input, need_filter, workspace, grad_input,
-                                      grad_filter, _raw_stream(_current_device()))
+                                      grad_filter, _stream_address)
     if status != OK:
         _check(status)
     return gi, gf

@@ -119,7 +119,18 @@ at::Tensor new_out(const at::Tensor& image, const at::Tensor& filt, int64_t c, i
   return at::empty({image.size(0), c, h, w}, opt);
 }
 
-void* stream_of(PyObject* o) { return PyLong_AsVoidPtr(o); }
+// The stream's address, or a function that returns it: the device is asked only
+// when the arguments are in order.
+bool stream_of(PyObject* o, void** out) {
+  THPObjectPtr made;
+  if (!PyLong_Check(o)) {
+    made = PyObject_CallObject(o, nullptr);
+    if (!made) return false;
+    o = made.get();
+  }
+  *out = PyLong_AsVoidPtr(o);
+  return !PyErr_Occurred();
+}
 
 PyObject* py_connect(PyObject*, PyObject* args) {
   PyObject* a[5];
@@ -147,7 +158,6 @@ PyObject* py_forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
   opts.epilogue = static_cast<int32_t>(PyLong_AsLong(a[3]));
   opts.variant = static_cast<int32_t>(PyLong_AsLong(a[6]));
   opts.border = static_cast<int32_t>(PyLong_AsLong(a[8]));
-  void* stream = stream_of(a[9]);
   if (PyErr_Occurred()) return nullptr;
   f2d_tensor x;
   if (!describe(image, &x)) return nullptr;
@@ -200,6 +210,8 @@ PyObject* py_forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Py_INCREF(a[5]);
     list = a[5];
   }
+  void* stream;
+  if (!stream_of(a[9], &stream)) return nullptr;
   f2d_status st;
   {
     pybind11::gil_scoped_release nogil;
@@ -221,7 +233,6 @@ PyObject* py_upsample(PyObject*, PyObject* const* a, Py_ssize_t n) {
   f2d_opts opts{};
   opts.channels = F2D_CH_SHARED;
   opts.border = static_cast<int32_t>(PyLong_AsLong(a[5]));
-  void* stream = stream_of(a[6]);
   if (PyErr_Occurred()) return nullptr;
   f2d_tensor x, y;
   if (!describe(image, &x)) return nullptr;
@@ -236,6 +247,8 @@ PyObject* py_upsample(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Py_INCREF(a[3]);
     out = a[3];
   }
+  void* stream;
+  if (!stream_of(a[6], &stream)) return nullptr;
   f2d_status st;
   {
     pybind11::gil_scoped_release nogil;
@@ -271,7 +284,6 @@ PyObject* py_separable(PyObject*, PyObject* const* a, Py_ssize_t n) {
     opts.row_begin = PyLong_AsLongLong(a[3]);
     opts.row_end = PyLong_AsLongLong(a[4]);
   }
-  void* stream = stream_of(a[6]);
   if (PyErr_Occurred()) return nullptr;
   THPObjectPtr out;
   if (a[5] == Py_None) {
@@ -285,6 +297,8 @@ PyObject* py_separable(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Py_INCREF(a[5]);
     out = a[5];
   }
+  void* stream;
+  if (!stream_of(a[6], &stream)) return nullptr;
   f2d_status st;
   {
     const float* pa = static_cast<const float*>(fa.data_ptr());
@@ -318,7 +332,6 @@ PyObject* py_backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
   f2d_opts opts{};
   opts.channels = static_cast<int32_t>(PyLong_AsLong(a[3]));
   const bool need_x = PyObject_IsTrue(a[4]) == 1, need_f = PyObject_IsTrue(a[5]) == 1;
-  void* stream = stream_of(a[9]);
   if (PyErr_Occurred()) return nullptr;
   const auto f32 = at::TensorOptions().dtype(at::kFloat).device(image.device());
   THPObjectPtr gi, gf;
@@ -359,6 +372,8 @@ PyObject* py_backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (!ws.defined() || static_cast<size_t>(ws.numel()) < bytes)
     ws = at::empty({static_cast<int64_t>(bytes > 1 ? bytes : 1)},
                    at::TensorOptions().dtype(at::kByte).device(image.device()));
+  void* stream;
+  if (!stream_of(a[9], &stream)) return nullptr;
   f2d_status st;
   {
     void* wp = ws.data_ptr();

@@ -128,3 +128,22 @@ def test_outputs_made_by_a_sequence_live_until_the_call(native, hooked):
     hooked(filter2d_forward=lambda *a: alive.append([r() is not None for r in Fresh.refs]) or B.OK)
     status, outs = fwd(native, filt=torch.zeros(6, 1, 3, 3), mode=1, outs=Fresh())
     assert status == B.OK and alive == [[True, True]] and isinstance(outs, Fresh)
+
+
+def test_argument_errors_come_before_the_device(native, monkeypatch):
+    def no_device(*_):
+        raise RuntimeError("no device")
+
+    monkeypatch.setattr(B, "_raw_stream", no_device)
+    monkeypatch.setattr(B, "_current_device", lambda: 0)
+    row, u8 = torch.zeros(5), IMG.byte()
+    for call in (lambda: B.forward(row, TAPS), lambda: B.upsample_forward(row.byte(), TAPS, 2),
+                 lambda: B.forward_separable(IMG, torch.zeros(3), torch.zeros(5)),
+                 lambda: B.backward(row, TAPS, row)):
+        with pytest.raises(ValueError):
+            call()
+    for call in (lambda: B.forward(IMG, TAPS), lambda: B.upsample_forward(u8, TAPS, 2),
+                 lambda: B.forward_separable(IMG, torch.zeros(3), torch.zeros(3)),
+                 lambda: B.backward(IMG, TAPS, IMG)):
+        with pytest.raises(RuntimeError, match="no device"):
+            call()
