@@ -11,6 +11,7 @@ instead of computing anything itself.
 """
 import ctypes
 import importlib
+import operator
 import os
 
 import torch
@@ -220,7 +221,7 @@ def upsample_forward(image, filt, scale, out=None, out_dtype=None, border="clamp
     if _native is None:
         load()
     b = _BORDERS[border] if isinstance(border, str) else int(border)
-    status, out = _native.upsample(image, filt, int(scale), out, out_dtype, b, _stream_address)
+    status, out = _native.upsample(image, filt, scale, out, out_dtype, b, _stream_address)
     if status != OK:
         _check(status)
     return out
@@ -231,7 +232,7 @@ def forward_separable(image, a, b, rows=None, out=None):
     current stream.  a, b: 1-D device tensors of k float32 taps."""
     if _native is None:
         load()
-    r0, r1 = (None, None) if rows is None else rows
+    r0, r1 = (None, None) if rows is None else map(operator.index, rows)
     status, out = _native.separable(image, a, b, r0, r1, out, _stream_address)
     if status != OK:
         _check(status)

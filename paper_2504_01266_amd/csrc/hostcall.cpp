@@ -229,7 +229,10 @@ PyObject* py_upsample(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const at::Tensor& filt = tensor_of(a[1], "filt");
   f2d_filter fd;
   if (!describe_filter(filt, &fd)) return nullptr;
-  const int64_t scale = PyLong_AsLongLong(a[2]);
+  // a new output takes whole factors only, a given one what int() takes
+  THPObjectPtr factor(a[3] == Py_None ? PyNumber_Index(a[2]) : PyNumber_Long(a[2]));
+  if (!factor) return nullptr;
+  const int64_t scale = PyLong_AsLongLong(factor.get());
   f2d_opts opts{};
   opts.channels = F2D_CH_SHARED;
   opts.border = static_cast<int32_t>(PyLong_AsLong(a[5]));

@@ -147,3 +147,20 @@ def test_argument_errors_come_before_the_device(native, monkeypatch):
                  lambda: B.backward(IMG, TAPS, IMG)):
         with pytest.raises(RuntimeError, match="no device"):
             call()
+
+
+def test_factors_and_rows_that_are_no_whole_numbers(native, hooked):
+    seen = []
+    hooked(filter2d_upsample_forward=lambda x, f, s, *_: seen.append(s) or B.OK,
+           filter2d_forward_separable=lambda x, a, b, k, o, *_: seen.append((o[0].row_begin, o[0].row_end)) or B.OK)
+    u8, taps = IMG.byte(), torch.zeros(3)
+    for scale in (2.5, 2.0, None):
+        with pytest.raises(TypeError):
+            B.upsample_forward(u8, TAPS, scale)
+    for rows in ((None, None), (None, 4), (0, None), (0.0, 4.0)):
+        with pytest.raises(TypeError):
+            B.forward_separable(IMG, taps, taps, rows=rows)
+    assert seen == []
+    native.upsample(u8, TAPS, 2.5, torch.zeros(1, 3, 16, 18).byte(), None, 0, 0)  # a given output: int(scale)
+    native.separable(IMG, taps, taps, 2, 4, None, 0)
+    assert seen == [2, (2, 4)]
