@@ -12,6 +12,7 @@
 // Per output value the taps are accumulated in the order (source s, row u,
 // column v), independent of the tiling variant, so all variants give bitwise
 // identical results.
+#include "f2d_host.hpp"
 #include "f2d_internal.hpp"
 #include "stencil_tile.hpp"
 
@@ -309,7 +310,10 @@ int f32_variant_count() { return 4; }
 int f32_default_variant(int K, int64_t planes, int64_t rows, int64_t w) {
   const int64_t tiles = planes * ((rows + 63) / 64) * ((w + 63) / 64);
   if (tiles <= 512) return 2;
-  if (w >= 512 && (K == 9 || (K >= 5 && tiles < 8192))) return 4;
+  // A list of variant 1's tiles that one launch takes may be too long in
+  // variant 4's (513 columns and 33 to 64 rows: 10 tiles for 9).
+  const bool fits = planes * ((rows + 31) / 32) * ((w + 127) / 128) <= kMaxBlocks;
+  if (w >= 512 && fits && (K == 9 || (K >= 5 && tiles < 8192))) return 4;
   return 1;
 }
 
