@@ -108,7 +108,9 @@ typedef struct f2d_opts {
   int32_t border;   /* F2D_BORDER_CLAMP */
   int32_t channels; /* F2D_CH_* */
   int32_t epilogue; /* F2D_EPI_* */
-  int32_t variant;  /* 0: tuned / default tiling; > 0 forces a tiling variant */
+  int32_t variant;  /* 0: tuned / default tiling; > 0 forces a tiling variant
+                       (ignored where a path has one tiling, e.g. FP32 banks on
+                       the matrix cores) */
   /* Output rows [row_begin, row_end) of the INPUT buffer are produced
    * (row_end <= 0 means image->h).  A GPU that owns output rows [y0, y1) of an
    * image of height H passes the input rows [max(0,y0-r), min(H,y1+r)) as the
@@ -309,8 +311,9 @@ f2d_status filter2d_batched(const f2d_batch_item* items_dev, const int64_t* tile
  * Autotuner: times every tiling variant of the forward (resp. batched) call
  * for these arguments `reps` times with HIP events on `stream`, records the
  * fastest in the process-wide tuning table (keyed by path, dtype, K, channel
- * mode and image-width class) and returns it in *best_variant.  These calls
- * synchronise the stream and overwrite the outputs.
+ * mode and image-width class) and returns it in *best_variant.  FP32 banks on
+ * the matrix cores have one tiling: 1 is returned and nothing recorded.  These
+ * calls synchronise the stream and overwrite the outputs.
  */
 f2d_status filter2d_autotune_forward(const f2d_tensor* image, const f2d_filter* filter,
                                      const f2d_opts* opts, const f2d_tensor* outs,

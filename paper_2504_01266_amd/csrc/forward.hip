@@ -274,6 +274,14 @@ f2d_status autotune_forward(const Problem& pr, const f2d_tensor* outs, int32_t n
   int path = pr.image.dtype == F2D_U8 ? kPathU8 : (pr.image.dtype == F2D_F32 ? kPathF32 : -1);
   if (path < 0) return fail(F2D_EUNSUPPORTED, "autotune: no tiling variants for this dtype");
   if (reps < 1) return fail(F2D_EINVAL, "autotune: reps must be >= 1");
+  if (path == kPathF32 && bank_f32_conv_mfma(pr.mode, pr.k, pr.image.c, pr.c_out, pr.image.w)) {
+    // one tiling: nothing to time, and an entry would select the tiling of
+    // the VALU banks that share its key
+    if (f2d_status st = run_forward(pr, outs, n_outs, s)) return st;
+    if (hipStreamSynchronize(s) != hipSuccess) return fail(F2D_EHIP, "autotune: kernel failed");
+    if (best) *best = 1;
+    return ok();
+  }
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess) return fail(F2D_EHIP, "autotune: hipEventCreate failed");
   if (hipEventCreate(&e1) != hipSuccess) {

@@ -102,3 +102,17 @@ def test_weight_gradient_over_several_row_segments(gpu_lib, case):
     _, gf = gpu_lib.backward(dev(x), dev(f), dev(g), mode="bank", need_input=False)
     assert np.array_equal(gf.double().cpu().numpy(),
                           oracle.grad_filter(x.astype(np.float64), g.astype(np.float64), f.shape, "bank"))
+
+
+def test_autotuning_a_bank_with_one_tiling_records_nothing(gpu_lib, tmp_path):
+    """The FP32 banks on the matrix cores have no tiling variants: autotuning
+    one reports variant 1 and leaves the table alone (its key is shared with
+    VALU banks of few channels)."""
+    x, f = ints(15, 1, 16, 40, 70), ints(16, 64, 16, 3, 3)
+    gpu_lib.tune_clear()
+    try:
+        assert gpu_lib.autotune_forward(dev(x), dev(f), mode="bank") == 1
+        gpu_lib.tune_save(str(tmp_path / "tune.json"))
+        assert "[0, 2, 3, 2," not in (tmp_path / "tune.json").read_text()
+    finally:
+        gpu_lib.tune_clear()
