@@ -501,3 +501,39 @@ def test_narrow_rows_sum_in_the_order_of_wider_ones(gpu_lib, cio, w, k):
         gi_w, _ = gpu_lib.backward(x[..., cols].contiguous(), f, gw, mode="bank", need_filter=False)
         e = 1 if k > 1 else 0
         assert torch.equal(gi[..., e:h - e, e:w - e], gi_w[..., e:h - e, 8 + e:8 + w - e])
+
+
+@pytest.mark.parametrize("cout", [16, 24])
+@pytest.mark.parametrize("k", [1, 3, 5])
+def test_row_ring_without_planned_offsets(gpu_lib, cout, k):
+    """33 to 64 source channels in rows 2^24 elements apart, where the staging
+    offsets do not fit the ring kernel's 32-bit plan: several tile rows and a
+    chunk across the right end of the rows, as a forward (planes side by side
+    in the rows) and as a grad_input from 40 channels in either type."""
+    cin, h, w = 40, 13, 77
+    r = wl.rng(71, cout, k)
+    pitch, plane = 2 ** 24, w + 3
+
+    def far_apart(vals, dtype):  # [1][c][h][w] values in rows `pitch` elements apart
+        buf = torch.zeros(h * pitch, dtype=dtype, device="cuda")
+        view = buf.as_strided((1, vals.shape[1], h, w), (h * pitch, plane, pitch, 1), 5)
+        view.copy_(torch.from_numpy(vals))
+        return view
+
+    ints = lambda *s: r.integers(-4, 5, s).astype(np.float32)  # noqa: E731
+    print(cout, k, flush=True)
+    x, f = ints(1, cin, h, w), ints(cout, cin, k, k)
+    xv = far_apart(x, torch.bfloat16)
+    want = oracle.forward(x.astype(np.float64), f.astype(np.float64), "bank")
+    for dt in (torch.float32, torch.bfloat16):
+        got = gpu_lib.forward(xv, bf(f)[0], mode="bank", out_dtype=dt)
+        assert torch.equal(got.cpu(), torch.from_numpy(want).float().to(dt))
+    del xv
+    if cout > 16:
+        return
+    g, fb = ints(1, cin, h, w), ints(cin, cout, k, k)
+    want = oracle.grad_input(g.astype(np.float64), fb.astype(np.float64), (1, cout, h, w), "bank")
+    xs = torch.zeros(1, cout, h, w, dtype=torch.bfloat16, device="cuda")
+    for dt in (torch.bfloat16, torch.float32):
+        gi, _ = gpu_lib.backward(xs, bf(fb)[0], far_apart(g, dt), mode="bank", need_filter=False)
+        assert_same(host(gi), want)
