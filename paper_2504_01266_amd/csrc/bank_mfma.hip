@@ -1581,8 +1581,10 @@ __device__ __forceinline__ void wg_rows(f32x4 (&acc)[K * K], const bf16x8 (&ga)[
 // K*K taps (acc).  Per tile: stage the clamped X tile in LDS (channel planes,
 // 16-byte chunks), then for each 32-pixel step hold the 8 G-bar row
 // fragments in registers and sweep the LH source rows once.
+// (Element staging, VEC = false, spills at three waves per SIMD: grad_filter of 64
+// x 3 x 512 x 7 -> 16, 3x3, 115 us, 102 at two)
 template <int K, typename TG, bool VEC>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(K <= 3 ? 3 : 2))) void k_bank_wgrad(WgradParams p) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(VEC ? (K == 1 ? 4 : (K == 3 ? 3 : 2)) : 2))) void k_bank_wgrad(WgradParams p) {
   using G = WgGeom<K>;
   static_assert(G::R <= 4, "K <= 9");
   __shared__ uint4 xs4[(G::ELEMS + 7) / 8];
