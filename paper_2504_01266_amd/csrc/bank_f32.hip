@@ -709,15 +709,27 @@ bool bank_f32_conv_mfma(int mode, int K, int64_t src, int64_t out, int64_t w) {
 // grad_filter pads both channel counts to sixteens.  Measured as above: 1x1
 // 3 x 16 1.6, 8 x 8 1.1, 1 x 64 0.8; 3x3 8 x 16 1.24, 8 x 8 0.83, 16 x 64
 // 2.8; 5x5 8 x 16 0.8, 16 x 16 1.2, 16 x 64 1.9.
-// Small 1x1 layers stay on the VALU, whose fewer partial sets are added sooner
-// (multiply-adds 0.4M 15.8 / 20.3 us, 0.9M 16.0 / 18.9, 13M 32.6 / 33.5, 18M
-// 27.0 / 25.2, 28M 36.0 / 25.5); 3x3 with 32M: 32.8 / 27.7.
+// Small layers stay on the VALU, whose fewer partial sets are added sooner
+// (VALU / matrix us):
+// - 1x1 by multiply-adds: 0.4M 15.8 / 20.3, 0.9M 16.0 / 18.9, 13M 32.6 / 33.5,
+//   18M 27.0 / 25.2, 28M 36.0 / 25.5.
+// - 3x3 and 5x5 by the VALU kernel's work, 64 x 64 tiles times channel pairs
+//   times images: it takes about as long up to 4096 of them as for 500, at any
+//   number of pixels in them.  5x5: 1024 35 / 54 (16 -> 16, 112^2), 2304 41 / 75
+//   (160^2), 4096 68 / 76 (16 -> 16) but 65 / 62 (16 -> 64, 112^2) and 65 / 43 (64
+//   -> 64, 14^2), 6144 73 / 82 (48 -> 16) and 77 / 74 (12 -> 16), 8192 103 / 73.
+//   3x3 likewise (2048 31 / 38, 16 -> 16; 4096 33 / 39, 16 -> 32; 6144 36 / 39, 48
+//   -> 16, and 40 / 38, 12 -> 16; 8192 60 / 36), except where the rows and strips
+//   of all images are few, and with them the partial sets: 14 rows 29 / 19, 224
+//   rows 31 / 29 (16 -> 16; 400 rows 32 / 38).
 bool bank_f32_wgrad_mfma(int mode, int K, int64_t co, int64_t ci, int64_t n, int64_t h, int64_t w) {
   if (mode != F2D_CH_BANK || w < 4 || ci > 65536 || co > 65536) return false;
   const int64_t pairs = ci * co, padded = (ci + 15) / 16 * 16 * ((co + 15) / 16 * 16);
-  if (K == 1) return 16 * pairs >= 3 * padded && static_cast<double>(pairs) * n * h * w >= 16e6;
-  if (K == 3) return 2 * pairs >= padded;
-  if (K == 5) return 4 * pairs >= 3 * padded;
+  const double pixels = static_cast<double>(n) * h * w, rows = static_cast<double>(n) * h * ((w + 63) / 64);
+  const double tiles = static_cast<double>(n) * ((h + 63) / 64) * ((w + 63) / 64) * pairs;
+  if (K == 1) return 16 * pairs >= 3 * padded && pairs * pixels >= 16e6;
+  if (K == 3) return 2 * pairs >= padded && (tiles >= 8192 || rows <= 256);
+  if (K == 5) return 4 * pairs >= 3 * padded && (tiles >= 8192 || (tiles >= 4096 && pairs >= 1024));
   return false;
 }
 
