@@ -143,7 +143,7 @@ f2d_status run_backward(const Problem& pr, const f2d_tensor* grad_outs, int32_t 
   const bool empty = im.n == 0 || im.c == 0 || im.h == 0 || im.w == 0 || co == 0;
 
   // ---------------------------------------------------------- grad_input --
-  if (grad_input && !empty && bank_f32_conv_mfma(pr.mode, K, pr.c_out, im.c, im.w)) {
+  if (grad_input && !empty && bank_f32_adjoint_mfma(pr.mode, K, pr.c_out, im.c, im.n, im.h, im.w)) {
     const f2d_tensor& g = grad_outs[0];
     const int64_t r = (K - 1) / 2;
     BankF32Params p;

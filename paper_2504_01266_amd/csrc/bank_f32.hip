@@ -14,7 +14,7 @@
 // forward 6.25 -> 2.88 ms (107 TFLOP/s, matrix cores busy 77% of the cycles),
 // grad_input 7.32 -> 3.1 ms, grad_filter 8.68 -> 2.95 ms against the VALU
 // kernels, which stay for shapes that the padding to 4 x 16 channels makes
-// slower here (bank_f32_conv_mfma, bank_f32_wgrad_mfma).
+// slower here (bank_f32_conv_mfma, bank_f32_adjoint_mfma, bank_f32_wgrad_mfma).
 //
 //  k_bank_f32_wgrad  F-bar[o][c][u][v] = sum_p G[o][p] X[c][p + (u, v)]: per
 //                    tap a 16 x 16 block of (output, source) channels
@@ -697,11 +697,47 @@ hipError_t wgrad_go(BankF32WgradParams p, hipStream_t s) {
 // matrix time, forward): 1x1 3 -> 16 1.2, 16 -> 3 2.1, 4 -> 4 0.85; 3x3 3 ->
 // 16 1.2, 8 -> 8 1.04, 16 -> 3 1.05, 4 -> 4 0.64, 1 -> 64 0.8, 64 -> 1 0.6,
 // 16 -> 64 2.0; 5x5 8 -> 8 1.02, 16 -> 3 0.6, 1 -> 64 0.7, 16 -> 64 2.0.
-bool bank_f32_conv_mfma(int mode, int K, int64_t src, int64_t out, int64_t w) {
+//
+// The VALU kernels take four outputs (of a multiple of four, and not with zero
+// borders) from one staged tile, so on many tiles they win back some of these
+// (VALU / matrix us):
+// - 3x3 with less than half of the padded products real: 64 -> 4 8 x 512^2 220 /
+//   345, 6 -> 8 45 / 54, 5 -> 12 4 x 1024^2 100 / 104, 64 -> 8 717 / 695; from two
+//   channels 2 -> 32 144 / 159;
+// - 1x1 on narrow images, whose tiles are mostly border: 64 x 512 x 24, 64 -> 4 74
+//   / 119, 4 -> 64 90 / 113; 3 -> 32 at any width (8 x 512^2 65 / 69);
+// - grad_input into many channels from few, bound by stores that start 4 columns
+//   left of the lines: 8 x 512^2 3 -> 64 293 / 386, 4 -> 64 348 / 391, and of narrow
+//   images: 64 x 512 x 48 16 -> 3 129 / 162, 8 -> 8 97 / 108.
+// On few tiles the VALU leaves the GPU idle (64 -> 4, 4 x 224^2 150 / 54).  A
+// forward takes one kernel for every height and batch all the same: row bands
+// have the bits of the whole image.  A grad_input is of whole images.
+bool bank_f32_conv_mfma(int mode, int K, int64_t src, int64_t out, int64_t w, bool zero) {
   if (mode != F2D_CH_BANK || w < 4 || src > 65536 || out > 65536) return false;
   const int64_t pairs = src * out, padded = (src + 3) / 4 * 4 * ((out + 15) / 16 * 16);
-  if (K == 1) return src >= 3 && pairs >= 32;
-  if (K == 3) return src >= 2 && pairs >= 48 && 16 * pairs >= 3 * padded;
+  const bool fours = out % 4 == 0 && !zero;
+  if (K == 1)
+    return src >= 3 && pairs >= 32 &&
+           !(fours && ((w < 128 && pairs <= 256) || (src <= 4 && out > 16 && out <= 32)));
+  if (K == 3)
+    return src >= 2 && pairs >= 48 && 16 * pairs >= 3 * padded && !(fours && (src < 3 || 2 * pairs < padded));
+  if (K == 5) return src >= 2 && pairs >= 48 && 2 * pairs >= padded;
+  return false;
+}
+
+bool bank_f32_adjoint_mfma(int mode, int K, int64_t src, int64_t out, int64_t n, int64_t h, int64_t w) {
+  if (mode != F2D_CH_BANK || w < 4 || src > 65536 || out > 65536) return false;
+  const int64_t pairs = src * out, padded = (src + 3) / 4 * 4 * ((out + 15) / 16 * 16);
+  const bool fours = out % 4 == 0;
+  const double groups = static_cast<double>(n) * ((h + 63) / 64) * ((w + 63) / 64) * (fours ? out / 4 : out);
+  const bool full = groups >= 256;  // the VALU's work-groups fill the GPU
+  if (K == 1)
+    return src >= 3 && pairs >= 32 &&
+           !(fours && src <= 4 && w < 128) &&
+           !(full && ((w < 128 && pairs <= 256) || (fours && src <= 4 && out > 16 && out <= 32)));
+  if (K == 3)
+    return src >= 2 && pairs >= 48 && 16 * pairs >= 3 * padded &&
+           !(full && ((fours && 2 * pairs < padded) || (fours && src <= 4 && out >= 32) || (w < 128 && pairs <= 96)));
   if (K == 5) return src >= 2 && pairs >= 48 && 2 * pairs >= padded;
   return false;
 }

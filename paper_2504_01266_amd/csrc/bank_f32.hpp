@@ -49,9 +49,10 @@ struct BankF32WgradParams {
   int32_t obw, ibw, i_groups, block_groups;
 };
 
-// Whether a map from src to out channels, or a grad_filter, of this shape
-// takes these kernels (else the VALU ones).
-bool bank_f32_conv_mfma(int mode, int K, int64_t src, int64_t out, int64_t w);
+// Whether a forward or its adjoint in the image, from src to out channels, or a
+// grad_filter, of this shape takes these kernels (else the VALU ones).
+bool bank_f32_conv_mfma(int mode, int K, int64_t src, int64_t out, int64_t w, bool zero);
+bool bank_f32_adjoint_mfma(int mode, int K, int64_t src, int64_t out, int64_t n, int64_t h, int64_t w);
 bool bank_f32_wgrad_mfma(int mode, int K, int64_t co, int64_t ci, int64_t n, int64_t h, int64_t w);
 void bank_f32_wgrad_plan(int64_t n, int64_t h, int64_t w, int64_t co, int64_t ci, int64_t max_sets,
                          BankF32WgradPlan* plan);

@@ -133,8 +133,12 @@ f2d_status forward_bank_f32(const Problem& pr, const f2d_tensor& out, hipStream_
   return hip_status(launch_bank_f32_conv(p, pr.k, false, s), "forward f32 bank launch");
 }
 
+bool on_matrix_cores(const Problem& pr) {
+  return bank_f32_conv_mfma(pr.mode, pr.k, pr.image.c, pr.c_out, pr.image.w, pr.opts.border == F2D_BORDER_ZERO);
+}
+
 f2d_status forward_f32(const Problem& pr, const f2d_tensor* outs, int32_t n_outs, hipStream_t s) {
-  if (bank_f32_conv_mfma(pr.mode, pr.k, pr.image.c, pr.c_out, pr.image.w)) return forward_bank_f32(pr, outs[0], s);
+  if (on_matrix_cores(pr)) return forward_bank_f32(pr, outs[0], s);
   if (pr.opts.border == F2D_BORDER_ZERO) return forward_f32_zero(pr, outs, s);
   const int K = pr.k;
   const bool templ = K <= kMaxTemplK;
@@ -274,7 +278,7 @@ f2d_status autotune_forward(const Problem& pr, const f2d_tensor* outs, int32_t n
   int path = pr.image.dtype == F2D_U8 ? kPathU8 : (pr.image.dtype == F2D_F32 ? kPathF32 : -1);
   if (path < 0) return fail(F2D_EUNSUPPORTED, "autotune: no tiling variants for this dtype");
   if (reps < 1) return fail(F2D_EINVAL, "autotune: reps must be >= 1");
-  if (path == kPathF32 && bank_f32_conv_mfma(pr.mode, pr.k, pr.image.c, pr.c_out, pr.image.w)) {
+  if (path == kPathF32 && on_matrix_cores(pr)) {
     // one tiling: nothing to time, and an entry would select the tiling of
     // the VALU banks that share its key
     if (f2d_status st = run_forward(pr, outs, n_outs, s)) return st;
