@@ -604,8 +604,11 @@ hipError_t launch_reduce_partials(float* partial, float* out, int64_t nf, int kk
   // more floats apart, so beyond some 64k values the coalesced first pass pays
   // for its launch and its 32 dependent steps).  grad_filter of 3 x 240 x 320
   // 3x3 14.1 -> 8.9 us, 3 x 511 x 767 3x3 18.3 -> 10.6, 9x9 31.0 -> 22.9, 4 x 3 x
-  // 1024^2 3x3 (27648 values) 29.5 -> 27.3.
-  if (count > 0 && m * count <= 65536) {
+  // 1024^2 3x3 (27648 values) 29.5 -> 27.3.  Outputs up to what the GPU holds
+  // work-groups of this size (2304 outputs of 1 set 10.4 -> 10.2 us); with more,
+  // each adds few values and a thread per output is faster: 9216 outputs of 1
+  // set 14.5 (17.3 in one launch), 65536 of 1 86 (123), 6400 of 8 28.1 (29.1).
+  if (count > 0 && m <= 2304 && m * count <= 65536) {
     hipLaunchKernelGGL(k_reduce_rows, dim3(static_cast<uint32_t>(m)), dim3(256), 0, s, partial, out, nf, kk,
                        chunks, count, int64_t{1});
     return hipGetLastError();

@@ -18,3 +18,13 @@ def test_shared_filter_over_many_planes(gpu_lib, planes):
     print(planes, flush=True)
     _, gf = gpu_lib.backward(*(torch.from_numpy(a).cuda() for a in (x, f, g)), need_input=False)
     np.testing.assert_array_equal(gf.cpu().numpy(), oracle.grad_filter(x, g, (1, 1, 3, 3), "shared")[0, 0])
+
+
+@pytest.mark.parametrize("channels", [255, 256, 257])  # 9 taps x 256 = 2304 outputs, one partial set each
+def test_depthwise_filters_by_the_number_of_outputs(gpu_lib, channels):
+    r = wl.rng(84, channels)
+    x, g = (r.integers(-4, 5, (2, channels, 6, 7)).astype(np.float32) for _ in range(2))
+    f = np.zeros((channels, 1, 3, 3), np.float32)
+    print(channels, flush=True)
+    _, gf = gpu_lib.backward(*(torch.from_numpy(a).cuda() for a in (x, f, g)), mode="depthwise", need_input=False)
+    np.testing.assert_array_equal(gf.cpu().numpy(), oracle.grad_filter(x, g, f.shape, "depthwise"))
