@@ -936,9 +936,12 @@ f2d_status gather_forward(const Problem& pr, const f2d_tensor& out, int32_t scal
   if (L > (int64_t{1} << 30) || g.Hout > (int64_t{1} << 30))
     return fail(F2D_EUNSUPPORTED, "u8 filter: output rows of at most 2^30 elements and 2^30 rows");
   // 3 x 3 into bytes, factors to 4: k_u8_direct (4K interleaved, gather /
-  // direct: x1 36 / 27 us, x2 76 / 35, x3 134 / 75, x4 199 / 113).  Larger
-  // factors are bound by their stores either way and stay with the gather.
-  if (pr.k == 3 && ok_out == kOutU8 && scale <= 4) {
+  // direct: x1 36 / 28 us, x2 76 / 35, x3 134 / 75, x4 199 / 107).  Larger
+  // factors are bound by their stores either way and stay with the gather, and
+  // so do images of fewer than 32 columns, all of whose waves hold an end of
+  // the rows and load by bytes (64 x 3 x 5^2 x1 8.9 / 11.4, 64 x 3 x 30^2 x3 22.4 /
+  // 26.2, 64 x 4 x 30^2 x3 18.9 / 32.6; none slower from 33 on).
+  if (pr.k == 3 && ok_out == kOutU8 && scale <= 4 && im.w >= 32) {
     DirectParams d;
     std::memset(&d, 0, sizeof(d));
     d.src = g.src;
