@@ -711,7 +711,9 @@ struct MixParams {
 constexpr int kMixThreads = 256;
 constexpr int kMixPx = 16;  // pixels per lane (measured: 8K gray 0.048 ms with 4)
 
-template <int CIN, bool TF, int OUT>
+// WHOLE: W is a multiple of a lane's 16 pixels (with the tests of the last lane
+// in it the kernel took 23.6 us on the 8K frame, 22.2 without).
+template <int CIN, bool TF, int OUT, bool WHOLE>
 __global__ __launch_bounds__(kMixThreads) void k_u8_mix(MixParams p) {
   using Acc = typename std::conditional<TF, float, uint32_t>::type;
   const int64_t b = xcd_remap(blockIdx.x, p.n_blocks);
@@ -721,7 +723,13 @@ __global__ __launch_bounds__(kMixThreads) void k_u8_mix(MixParams p) {
   const int64_t y = rem / p.tiles_x;
   const int64_t x0 = (rem - y * p.tiles_x) * (kMixThreads * kMixPx) + kMixPx * threadIdx.x;
   if (x0 >= p.W) return;
-  const bool full = x0 + kMixPx <= p.W;
+  // the row's last lane loads the 16 pixels that end with the row, and stores
+  // its own, [lo, hi) of them: a wave that also loaded by bytes paid for both
+  // (8-bit gray of 62 x 62: 4.15 us, 3.95 by bytes alone)
+  const bool full = WHOLE || p.W >= kMixPx;
+  const int64_t xs = !WHOLE && full && x0 + kMixPx > p.W ? p.W - kMixPx : x0;
+  const int lo = static_cast<int>(x0 - xs);
+  const int hi = full ? kMixPx : static_cast<int>(p.W - xs);
   const uint8_t* rp = p.src + n * p.s_sn + (p.row0 + y) * p.s_sh;
 
   // x[i][k]: channel i of pixel x0 + k
@@ -729,7 +737,7 @@ __global__ __launch_bounds__(kMixThreads) void k_u8_mix(MixParams p) {
   if (p.s_sw == CIN && p.s_sc == 1 && CIN > 1) {  // interleaved
     if (full) {
       uint32_t wd[CIN * kMixPx / 4];
-      load_words<CIN * kMixPx / 4>(rp + x0 * CIN, wd);
+      load_words<CIN * kMixPx / 4>(rp + xs * CIN, wd);
 #pragma unroll
       for (int k = 0; k < kMixPx; ++k)
 #pragma unroll
@@ -741,7 +749,7 @@ __global__ __launch_bounds__(kMixThreads) void k_u8_mix(MixParams p) {
 #pragma unroll
       for (int k = 0; k < kMixPx; ++k)
 #pragma unroll
-        for (int i = 0; i < CIN; ++i) x[i][k] = x0 + k < p.W ? rp[(x0 + k) * CIN + i] : 0u;
+        for (int i = 0; i < CIN; ++i) x[i][k] = k < hi ? rp[(xs + k) * CIN + i] : 0u;
     }
   } else {  // planar
 #pragma unroll
@@ -749,12 +757,12 @@ __global__ __launch_bounds__(kMixThreads) void k_u8_mix(MixParams p) {
       const uint8_t* cp = rp + i * p.s_sc;
       if (full) {
         uint32_t wd[kMixPx / 4];
-        load_words<kMixPx / 4>(cp + x0, wd);
+        load_words<kMixPx / 4>(cp + xs, wd);
 #pragma unroll
         for (int k = 0; k < kMixPx; ++k) x[i][k] = (wd[k >> 2] >> (8 * (k & 3))) & 0xffu;
       } else {
 #pragma unroll
-        for (int k = 0; k < kMixPx; ++k) x[i][k] = x0 + k < p.W ? cp[(x0 + k) * p.s_sw] : 0u;
+        for (int k = 0; k < kMixPx; ++k) x[i][k] = k < hi ? cp[(xs + k) * p.s_sw] : 0u;
       }
     }
   }
@@ -790,7 +798,7 @@ __global__ __launch_bounds__(kMixThreads) void k_u8_mix(MixParams p) {
         }
       }
       uint8_t* dp = static_cast<uint8_t*>(p.dst) + obase;
-      if (full && p.d_sw == 1) {
+      if (full && lo == 0 && p.d_sw == 1) {
         uint32_t ow[kMixPx / 4];
 #pragma unroll
         for (int q = 0; q < kMixPx / 4; ++q)
@@ -799,11 +807,11 @@ __global__ __launch_bounds__(kMixThreads) void k_u8_mix(MixParams p) {
       } else {
 #pragma unroll
         for (int k = 0; k < kMixPx; ++k)
-          if (x0 + k < p.W) dp[(x0 + k) * p.d_sw] = static_cast<uint8_t>(q8[k]);
+          if (k >= lo && k < hi) dp[(xs + k) * p.d_sw] = static_cast<uint8_t>(q8[k]);
       }
     } else {
       uint32_t* dp = static_cast<uint32_t*>(p.dst) + obase;
-      if (full && p.d_sw == 1) {
+      if (full && lo == 0 && p.d_sw == 1) {
         uint32_t ow[kMixPx];
 #pragma unroll
         for (int k = 0; k < kMixPx; ++k) ow[k] = __builtin_bit_cast(uint32_t, acc[k]);
@@ -811,7 +819,7 @@ __global__ __launch_bounds__(kMixThreads) void k_u8_mix(MixParams p) {
       } else {
 #pragma unroll
         for (int k = 0; k < kMixPx; ++k)
-          if (x0 + k < p.W) dp[(x0 + k) * p.d_sw] = __builtin_bit_cast(uint32_t, acc[k]);
+          if (k >= lo && k < hi) dp[(xs + k) * p.d_sw] = __builtin_bit_cast(uint32_t, acc[k]);
       }
     }
   }
@@ -995,17 +1003,21 @@ f2d_status gather_forward(const Problem& pr, const f2d_tensor& out, int32_t scal
   return hip_status(err, "u8 filter launch");
 }
 
-template <int CIN>
-hipError_t launch_mix_c(const MixParams& m, bool tf, int out, hipStream_t s) {
+template <int CIN, bool WHOLE>
+hipError_t launch_mix_w(const MixParams& m, bool tf, int out, hipStream_t s) {
   const dim3 grid(static_cast<uint32_t>(m.n_blocks)), block(kMixThreads);
   if (tf) {
-    if (out == kOutU8) hipLaunchKernelGGL((k_u8_mix<CIN, true, kOutU8>), grid, block, 0, s, m);
-    else hipLaunchKernelGGL((k_u8_mix<CIN, true, kOutF32>), grid, block, 0, s, m);
+    if (out == kOutU8) hipLaunchKernelGGL((k_u8_mix<CIN, true, kOutU8, WHOLE>), grid, block, 0, s, m);
+    else hipLaunchKernelGGL((k_u8_mix<CIN, true, kOutF32, WHOLE>), grid, block, 0, s, m);
   } else {
-    if (out == kOutU8) hipLaunchKernelGGL((k_u8_mix<CIN, false, kOutU8>), grid, block, 0, s, m);
-    else hipLaunchKernelGGL((k_u8_mix<CIN, false, kOutI32>), grid, block, 0, s, m);
+    if (out == kOutU8) hipLaunchKernelGGL((k_u8_mix<CIN, false, kOutU8, WHOLE>), grid, block, 0, s, m);
+    else hipLaunchKernelGGL((k_u8_mix<CIN, false, kOutI32, WHOLE>), grid, block, 0, s, m);
   }
   return hipGetLastError();
+}
+template <int CIN>
+hipError_t launch_mix_c(const MixParams& m, bool tf, int out, hipStream_t s) {
+  return m.W % kMixPx == 0 ? launch_mix_w<CIN, true>(m, tf, out, s) : launch_mix_w<CIN, false>(m, tf, out, s);
 }
 
 // BANK with K = 1 on an 8-bit image: per-pixel channel mixing.
