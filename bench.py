@@ -34,6 +34,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0           # MI355X HBM3E
 FP32_VALU_PEAK_TFLOPS = 78.6    # unpacked FP32 FMA: 256 CU x 64 lanes x 2 FLOP x 2.4 GHz
+FP32_MFMA_PEAK_TFLOPS = 157.3   # FP32 matrix cores: 256 CU x 256 FLOP x 2.4 GHz
 BF16_MFMA_PEAK_TFLOPS = 2516.6  # dense BF16 matrix cores
 
 BANK_N, BANK_CI, BANK_CO, BANK_HW = 32, 16, 64, 1024
@@ -552,7 +553,7 @@ def suite(torch, B, wl, reps, only=None):
             torch.cuda.empty_cache()
 
     if want('bank_f32'):
-        # the same 32-image bank in FP32 (matrix cores in FP32; fractions of the VALU's rate)
+        # the same 32-image bank in FP32 (matrix cores in FP32)
         for k in (3, 5):
             bt = bank_tensors(torch, wl, k, fp32=True)
             x32, g32, w32 = bt["x32"], bt["g32"], bt["w32"]
@@ -568,8 +569,8 @@ def suite(torch, B, wl, reps, only=None):
                                      "fwd_ms": round(ms_f, 3), "bwd_ms": round(ms_b, 3),
                                      "fwd_mpix_taps_s": round(bb["taps"] / (ms_f * 1e-3) / 1e6, 1),
                                      "fwd_bwd_mpix_taps_s": round(3 * bb["taps"] / ((ms_f + ms_b) * 1e-3) / 1e6, 1),
-                                     "fwd_valu_frac": round(bb["flops"] / (ms_f * 1e-3) / 1e12 / FP32_VALU_PEAK_TFLOPS, 4),
-                                     "bwd_valu_frac": round(2 * bb["flops"] / (ms_b * 1e-3) / 1e12 / FP32_VALU_PEAK_TFLOPS, 4)}
+                                     "fwd_mfma_frac": round(bb["flops"] / (ms_f * 1e-3) / 1e12 / FP32_MFMA_PEAK_TFLOPS, 4),
+                                     "bwd_mfma_frac": round(2 * bb["flops"] / (ms_b * 1e-3) / 1e12 / FP32_MFMA_PEAK_TFLOPS, 4)}
             del x32, g32, w32, y, gi, ws
             torch.cuda.empty_cache()
     return res

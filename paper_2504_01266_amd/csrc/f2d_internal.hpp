@@ -75,7 +75,7 @@ TileShape f32_tile(int variant);
 TileShape u8_tile(int variant);
 int f32_variant_count();
 int f32_default_variant(int K, int64_t planes, int64_t rows, int64_t w);
-int batched_variant_count();  // ragged batch: 1..4 one tile per work-group, 5..8 pipelined
+int batched_variant_count();  // ragged batch: 1..4 one tile per work-group, 5..8 runs of four
 int u8_variant_count();
 
 // XCD-aware work-group ordering: the hardware hands work-groups to the 8 XCDs

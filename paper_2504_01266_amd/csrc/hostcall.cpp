@@ -2,9 +2,9 @@
 // as f2d_tensor / f2d_filter, allocates the outputs the caller did not give
 // and calls the C ABI.  Built as the extension module _hostcall.
 //
-// A small filter's kernel takes about 6 us, and marshalling the call in
-// Python (ctypes structures, views, shape and stride look-ups) took 11 of the
-// 14.5 us of a call on a 64 x 64 image; here it takes about 3.
+// Marshalling in Python (ctypes structures, views, shape and stride look-ups)
+// took 11 of the 14.5 us of a 5x5 filter's call on 1 x 3 x 64 x 64; here it takes
+// 1.6 of 5, of which a new output is 1.0 and the current stream 0.35.
 //
 // Errors are those of the ctypes binding: ValueError for tensors the
 // descriptors cannot express, KeyError for element types the library does not

@@ -87,11 +87,8 @@ __device__ __forceinline__ float* dst_plane(const StencilParams& p, int t, int64
 // addresses are scalar and each load is scalar base + 32-bit lane offset.
 // This shortens single-output kernels; kernels that stage many source planes
 // per tile keep the per-lane form, which measured faster there.
-//
-// SP is the source pointer type: a plain pointer, or one qualified with the
-// global address space where the compiler cannot infer it.
-template <int K, int PX, int PY, bool ADJ, bool UNI = true, typename SP = const float*>
-__device__ __forceinline__ void stage_tile(float* __restrict__ lds, SP __restrict__ sp,
+template <int K, int PX, int PY, bool ADJ, bool UNI = true>
+__device__ __forceinline__ void stage_tile(float* __restrict__ lds, const float* __restrict__ sp,
                                            int64_t sh, int64_t H, int64_t W, int64_t row_base,
                                            int64_t col_base) {
   using G = Geom<K, PX, PY>;
@@ -127,7 +124,7 @@ __device__ __forceinline__ void stage_tile(float* __restrict__ lds, SP __restric
       const int ly = wave + kWaves * i;
       const int64_t gy = row_base - G::R + (ly < G::LH ? ly : G::LH - 1);
       rval[i] = gy >= 0 && gy < H;
-      const SP rp = sp + (rval[i] ? gy : 0) * sh;
+      const float* rp = sp + (rval[i] ? gy : 0) * sh;
 #pragma unroll
       for (int j = 0; j < CPL; ++j) buf[i][j] = rp[coff[j]];
     }
@@ -147,7 +144,7 @@ __device__ __forceinline__ void stage_tile(float* __restrict__ lds, SP __restric
       const int ly = wave + kWaves * i;
       int64_t gy = row_base - G::R + (ly < G::LH ? ly : G::LH - 1);
       gy = gy < 0 ? 0 : (gy >= H ? H - 1 : gy);
-      const SP rp = sp + gy * sh;
+      const float* rp = sp + gy * sh;
 #pragma unroll
       for (int j = 0; j < CPL; ++j) buf[i][j] = rp[coff[j]];
     }
@@ -209,7 +206,8 @@ __device__ __forceinline__ void store4(__attribute__((address_space(1))) float* 
 // bytes apart, for the rows of odd widths a ragged batch of 32 images of 256 to
 // 4096 rows and columns took 1242 us with 3x3 filters (now 800) and 1280 us
 // with 5x5 (now 956); one image of 3 x 511 x 767, 3x3: 8.2 us (now 7.1).
-// DP: plain or global-address-space output pointer (see stage_tile).
+// DP: a plain output pointer, or one in the global address space where the
+// compiler cannot infer it (pointers read from the ragged batch's table).
 template <int PX, typename DP = float*>
 __device__ __forceinline__ void store_row(DP __restrict__ dp, int64_t x0, int64_t W, const float (&v)[PX]) {
   if (x0 + PX <= W) {
