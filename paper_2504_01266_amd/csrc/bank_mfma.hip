@@ -646,7 +646,8 @@ __device__ __forceinline__ void mfma_sweep(const uint16_t* w_pass, Src&& xsrc, i
 // MFMA operands: A = 16 pixels x 32 k (the source tile), B = 32 k x 16 output
 // channels (the weights), so D[pixel 4q + j][channel l16]: each lane holds 4
 // consecutive pixels of one output channel and writes them with one store.
-template <int K, int OT, int PT, int CG, int NW, bool ADJ, typename TS, bool OUT_BF16, bool VEC>
+// WHOLE: W is a multiple of 8 (no chunk crosses the row's end).
+template <int K, int OT, int PT, int CG, int NW, bool ADJ, typename TS, bool OUT_BF16, bool VEC, bool WHOLE>
 __global__ __launch_bounds__(64 * NW) void k_bank_conv(BankParams p) {
   using G = ConvGeom<K, OT, PT, CG, NW>;
   constexpr int HP = G::HP;
@@ -690,7 +691,7 @@ __global__ __launch_bounds__(64 * NW) void k_bank_conv(BankParams p) {
   Raw<TS, G::NT> st;
   stage_load<G, K, CG, ADJ, TS, NW, G::LH, VEC>(p, n, oy0, ox0, wave, lane, st);
   load_weights<G, K, OT, CG, ADJ>(p, og, tid, wl);
-  stage_store<G, K, CG, ADJ, TS, NW, G::LH, false, VEC>(p, oy0, ox0, wave, lane, st, sl0);
+  stage_store<G, K, CG, ADJ, TS, NW, G::LH, false, VEC, WHOLE>(p, oy0, ox0, wave, lane, st, sl0);
   __syncthreads();
 
   int cur = 0;
@@ -738,8 +739,8 @@ __global__ __launch_bounds__(64 * NW) void k_bank_conv(BankParams p) {
       // is done reading (uniform branch)
       if (og2 != og || G::NBUF == 1) __syncthreads();
       if (og2 != og) load_weights<G, K, OT, CG, ADJ>(p, og2, tid, wl);
-      if constexpr (G::NBUF == 2) stage_fix<G, K, CG, ADJ, TS, NW, G::LH, false, VEC>(p, oy2, ox2, wave, lane, st, sl_next);
-      if constexpr (G::NBUF == 1) stage_store<G, K, CG, ADJ, TS, NW, G::LH, false, VEC>(p, oy2, ox2, wave, lane, st, sl0);
+      if constexpr (G::NBUF == 2 && !WHOLE) stage_fix<G, K, CG, ADJ, TS, NW, G::LH, false, VEC>(p, oy2, ox2, wave, lane, st, sl_next);
+      if constexpr (G::NBUF == 1) stage_store<G, K, CG, ADJ, TS, NW, G::LH, false, VEC, WHOLE>(p, oy2, ox2, wave, lane, st, sl0);
     }
     __syncthreads();  // tile t+1 staged; everyone done with buffer cur
     if (!more) break;
@@ -1728,7 +1729,7 @@ hipError_t conv_vr_go(const BankParams& pin, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int K, int OT, int PT, int CG, int NW, bool ADJ, typename TS, bool OB, bool VEC = true>
+template <int K, int OT, int PT, int CG, int NW, bool ADJ, typename TS, bool OB, bool VEC = true, bool WHOLE = false>
 hipError_t conv_go(const BankParams& pin, hipStream_t s) {
   using G = ConvGeom<K, OT, PT, CG, NW>;
   BankParams p = pin;
@@ -1750,7 +1751,7 @@ hipError_t conv_go(const BankParams& pin, hipStream_t s) {
       if constexpr (RING)
         kern = reinterpret_cast<const void*>(k_bank_conv_ring<K, OT, PT, CG, ADJ, TS, OB, VEC>);
       else
-        kern = reinterpret_cast<const void*>(k_bank_conv<K, OT, PT, CG, NW, ADJ, TS, OB, VEC>);
+        kern = reinterpret_cast<const void*>(k_bank_conv<K, OT, PT, CG, NW, ADJ, TS, OB, VEC, WHOLE>);
       e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
       if (e != hipSuccess) return e;
       int per_cu = 0, cus = 0;
@@ -1773,7 +1774,7 @@ hipError_t conv_go(const BankParams& pin, hipStream_t s) {
   else {
     const int64_t g = p.n_tiles < grid ? p.n_tiles : grid;
     if (g <= 0) return hipSuccess;
-    hipLaunchKernelGGL((k_bank_conv<K, OT, PT, CG, NW, ADJ, TS, OB, VEC>), dim3(static_cast<uint32_t>(g)),
+    hipLaunchKernelGGL((k_bank_conv<K, OT, PT, CG, NW, ADJ, TS, OB, VEC, WHOLE>), dim3(static_cast<uint32_t>(g)),
                        dim3(G::THREADS), lds, s, p);
     return hipGetLastError();
   }
@@ -1874,6 +1875,11 @@ hipError_t conv_by_shape(const BankParams& p, int ot, int cg, hipStream_t s) {
     if (ot == 2 && cg == 4) return conv_go<K, 2, 4, 4, 8, ADJ, TS, OB>(p, s);
     if (ot == 1 && cg == 4) return conv_go<K, 1, 4, 4, 8, ADJ, TS, OB>(p, s);
     if (ot == 2 && cg == 1) return conv_go<K, 2, 4, 1, 8, ADJ, TS, OB>(p, s);
+    if constexpr (K == 5) {
+      // (the fix-up of chunks at the rows' ends takes 5x5's registers past two
+      // work-groups per CU: 16 x 12 x 512^2 -> 24, BF16 out, 139 us, 152 with it)
+      if (ot == 2 && cg == 2 && p.W % 8 == 0) return conv_go<K, 2, 4, 2, 8, ADJ, TS, OB, true, true>(p, s);
+    }
     if (ot == 2 && cg == 2) return conv_go<K, 2, 4, 2, 8, ADJ, TS, OB>(p, s);
     if constexpr (K < 5) {
       if (ot == 2 && cg == 8) return conv_go<K, 2, 4, 8, 8, ADJ, TS, OB>(p, s);
