@@ -618,7 +618,8 @@ hipError_t launch_reduce_partials(float* partial, float* out, int64_t nf, int kk
   // work-groups of this size (2304 outputs of 1 set 10.4 -> 10.2 us); with more,
   // each adds few values and a thread per output is faster: 9216 outputs of 1
   // set 14.5 (17.3 in one launch), 65536 of 1 86 (123), 6400 of 8 28.1 (29.1).
-  if (count > 0 && m <= 2304 && m * count <= 65536) {
+  // Sets up to 16 a thread: 1 output of 6120 37.0 (39.8), of 7650 44.7 (49.8).
+  if (count > 0 && count <= 4096 && m <= 2304 && m * count <= 65536) {
     hipLaunchKernelGGL(k_reduce_rows, dim3(static_cast<uint32_t>(m)), dim3(256), 0, s, partial, out, nf, kk,
                        chunks, count, int64_t{1});
     return hipGetLastError();

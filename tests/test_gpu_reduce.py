@@ -28,3 +28,13 @@ def test_depthwise_filters_by_the_number_of_outputs(gpu_lib, channels):
     print(channels, flush=True)
     _, gf = gpu_lib.backward(*(torch.from_numpy(a).cuda() for a in (x, f, g)), mode="depthwise", need_input=False)
     np.testing.assert_array_equal(gf.cpu().numpy(), oracle.grad_filter(x, g, f.shape, "depthwise"))
+
+
+@pytest.mark.parametrize("planes", [4095, 4096, 4097])  # partial sets of one output
+def test_one_tap_over_many_planes(gpu_lib, planes):
+    r = wl.rng(85, planes)
+    x, g = (r.integers(-4, 5, (1, planes, 2, 3)).astype(np.float32) for _ in range(2))
+    print(planes, flush=True)
+    _, gf = gpu_lib.backward(*(torch.from_numpy(a).cuda() for a in (x, np.zeros((1, 1), np.float32), g)),
+                             need_input=False)
+    np.testing.assert_array_equal(gf.cpu().numpy(), oracle.grad_filter(x, g, (1, 1, 1, 1), "shared")[0, 0])
