@@ -11,10 +11,11 @@
 //
 // Bound by the matrix cores: 154.6 TFLOP/s in a large FP32 product on this
 // card (the clock falls to 2.2 GHz under it).  16 x 16 x 1024^2 -> 64, 3 x 3:
-// forward 6.25 -> 2.88 ms (107 TFLOP/s, matrix cores busy 77% of the cycles),
-// grad_input 7.32 -> 3.1 ms, grad_filter 8.68 -> 2.95 ms against the VALU
-// kernels, which stay for shapes that the padding to 4 x 16 channels makes
-// slower here (bank_f32_conv_mfma, bank_f32_adjoint_mfma, bank_f32_wgrad_mfma).
+// forward 6.25 -> 2.88 ms (107 TFLOP/s; at 32 images 6.2 ms with the matrix
+// cores busy 73% of the cycles at 2.1 GHz), grad_input 7.32 -> 3.1 ms,
+// grad_filter 8.68 -> 2.95 ms against the VALU kernels, which stay for shapes
+// that the padding to 4 x 16 channels makes slower here (bank_f32_conv_mfma,
+// bank_f32_adjoint_mfma, bank_f32_wgrad_mfma).
 //
 //  k_bank_f32_wgrad  F-bar[o][c][u][v] = sum_p G[o][p] X[c][p + (u, v)]: per
 //                    tap a 16 x 16 block of (output, source) channels
